@@ -20,12 +20,16 @@
 //      in fp64 across chunks;
 //   2. skips the pair if every column pair is already orthogonal to the
 //      tolerance (relative off-diagonal), otherwise
-//   3. reduces the small Gram by one sweep of two-sided Jacobi held in
+//   3. if every rotation the Gram asks for is small, takes them all at once
+//      (Theta = polar factor of I + E, four small matrix-core products), else
+//      reduces the small Gram by one sweep of two-sided Jacobi held in
 //      registers (fp32 entries, fp64 diagonal and angles; odd-even ordering,
 //      64 rounds of up to 32 disjoint rotations, accumulating the rotation
 //      Theta), and
 //   4. applies Theta to the pair's 64 columns of Y on the bf16 matrix cores,
 //      Theta and the 32-row chunks of Y split into three planes as in 1.
+// A launch of few workgroups runs them with four groups of four waves, the
+// row chunks of phases 1 and 4 dealt out to the groups (same bits).
 // A sweep is nb - 1 steps; the matrix has converged when a whole sweep
 // rotates nothing (rotation counts per sweep live in device memory, so no
 // host synchronisation is needed).
@@ -52,6 +56,7 @@ constexpr int JW = 2 * JB;         // columns per pair (64)
 constexpr int kInnerSweeps = GALORE_JAC_INNER;   // inner sweeps of a pair's 64 x 64 Gram per visit
 constexpr int JT = 256;            // threads (4 waves)
 constexpr int PD = JW + 1;         // padded LDS row
+constexpr int kPairWideMax = 256;  // workgroups up to which a step's launch takes the wide form (the CUs)
 
 static_assert(JW == 64, "the pair kernels assume 64 columns per pair");
 
@@ -266,18 +271,141 @@ __device__ __forceinline__ bf16x8 apply_frag(const unsigned char* lds, int s, in
 // (and the last sweeps are steered) at fp64 accuracy.
 typedef float jreal;
 
+// Angles at and below which a pair's rotations are taken all at once: every
+// |E_ij| <= kSmallAngle and the sum of E_ij^2 over i < j <= kSmallSum, i.e.
+// |E|_2 <= 0.15 (an antisymmetric matrix's singular values come in pairs).
+constexpr float kSmallAngle = 0.1f;
+constexpr float kSmallSum = 0.0225f;
+constexpr float kTinySum = 1.0f / 8192.0f;   // below: two products give Theta to fp32 rounding
+constexpr int SP = JW + 4;                   // row pitch of E and S (fp32): 16-byte rows, fragment reads on distinct banks
+
+// LDS of one group of four waves, reused phase by phase: two plane chunks, the
+// fp64 Gram, the inner sweep's exchange arrays, E and S, Theta
+constexpr int kPairLds = 2 * JW * SP * static_cast<int>(sizeof(float));
+static_assert(2 * kChunkBytes <= kPairLds && JW * PD * static_cast<int>(sizeof(double)) <= kPairLds, "phases fit");
+
+// Row chunks of segment g of four: [seg_begin(n, g), seg_begin(n, g + 1)). The
+// Gram is summed segment by segment (fp64), in the same order whether one
+// group of waves walks all four or four groups take one each.
+__device__ __forceinline__ int seg_begin(int nchunk, int g) { return (g * nchunk) >> 2; }
+
+// A step's rotations all at once. For columns i, j of the pair with Gram G a
+// Jacobi rotation of angle E_ij = g_ij / (g_jj - g_ii) removes g_ij to first
+// order; when all of them are small their joint rotation is the orthogonal
+// polar factor of I + E (E antisymmetric),
+//   Theta = (I + E)(I - E^2)^(-1/2) = (I + E)(I + S),
+//   S = P/2 + 3/8 P^2 + 5/16 P^3 + ...,  P = E^2,
+// off an orthogonal matrix by 35/128 |P|^4 < 7e-8. Second-order terms are left
+// for the next sweep, as a sweep of single rotations leaves them: in a CPU
+// model of these sweeps (six spectra, k = 136 .. 528, the exact SVD among
+// them) the number of sweeps is unchanged and the number of pair rotations
+// grows by 0-2%, and 40-60% of the pair visits take this form, the later
+// sweeps nearly all. fp32 matrix-core products (v_mfma_f32_16x16x4_f32), every
+// operand read by rows: P and S are symmetric and E is antisymmetric. On entry
+// E is in LDS; on exit Theta (fp32, row pitch PD) is. `tiles` of the 64 x 64
+// outputs: row tile wr, column tiles wc .. wc + NT - 1 of this wave.
+template <int NT>
+__device__ __forceinline__ void small_angle_theta(unsigned char* smem, int wr, int wc, int lane, bool tiny) {
+    float (*E)[SP] = reinterpret_cast<float (*)[SP]>(smem);
+    float (*S)[SP] = reinterpret_cast<float (*)[SP]>(smem + JW * SP * sizeof(float));
+    const int l15 = lane & 15, lk = lane >> 4;
+    float fe[16], fp[16];   // row 16 wr + l15 of E and of P, entries 4 s + lk
+    f32x4 acc[NT];
+    auto product = [&](const float* fa, const float (*B)[SP]) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[s], B[16 * (wc + t) + l15][4 * s + lk], acc[t], 0, 0, 0);
+    };
+    // a tile's rows 16 wr + 4 lk + v of column 16 (wc + t) + l15, stored as the
+    // four consecutive entries of that row of the (symmetric) matrix
+    auto store_sym = [&]() {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(&S[16 * (wc + t) + l15][16 * wr + 4 * lk]) = acc[t];
+    };
+    auto add_diag = [&](float c) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (wr == wc + t && l15 == 4 * lk + v) acc[t][v] += c;
+    };
+#pragma unroll
+    for (int s = 0; s < 16; ++s) fe[s] = E[16 * wr + l15][4 * s + lk];
+    product(fe, E);                                   // E E^T = -P
+    if (tiny) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] *= -0.5f;   // S = P / 2
+        store_sym();
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] *= -1.0f;
+        store_sym();
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < 16; ++s) fp[s] = S[16 * wr + l15][4 * s + lk];
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] *= 0.3125f;
+        add_diag(0.375f);
+        store_sym();                                  // 3/8 + 5/16 P
+        __syncthreads();
+        product(fp, S);
+        add_diag(0.5f);
+        __syncthreads();
+        store_sym();                                  // 1/2 + 3/8 P + 5/16 P^2
+        __syncthreads();
+        product(fp, S);
+        __syncthreads();
+        store_sym();                                  // S
+        __syncthreads();
+    }
+    f32x4 keep[NT];                                   // I + E + S, in the tiles' layout
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        keep[t] = *reinterpret_cast<const f32x4*>(&S[16 * (wc + t) + l15][16 * wr + 4 * lk]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * wr + 4 * lk + v, j = 16 * (wc + t) + l15;
+            keep[t][v] += E[i][j] + (i == j ? 1.0f : 0.0f);
+        }
+    }
+    product(fe, S);                                   // E S
+    __syncthreads();                                  // Theta overwrites E
+    float (*Tf)[PD] = reinterpret_cast<float (*)[PD]>(smem);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Tf[16 * wr + 4 * lk + v][16 * (wc + t) + l15] = keep[t][v] + acc[t][v];
+    __syncthreads();
+}
+
 // Step of the block Jacobi (one workgroup per pair and matrix): Gram of the
 // pair's 64 columns, convergence test, reduction of the small Gram, rotation
-// of the columns, all in one 64 x 65 fp64 LDS buffer (see below).
-__global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, int64_t strideX, int nb,
-                                                            int step, int sweep, int* rotb, int max_sweeps,
-                                                            double tol, int skip_dummy, const int* jpermb) {
+// of the columns, all in one LDS buffer per group of four waves (see above).
+// NG groups: 1, four workgroups per CU; or 4 (one workgroup per CU), for
+// launches whose workgroups do not outnumber the CUs: the chunk loops of the
+// two phases over memory wait a memory latency per chunk, which only other
+// workgroups of the CU would hide, so four groups walk a quarter of the chunks
+// each. The results are the same bits.
+template <int NG>
+__global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(float* Xtb, int k, int64_t strideX,
+                                                                               int nb, int step, int sweep, int* rotb,
+                                                                               int max_sweeps, double tol,
+                                                                               int skip_dummy, const int* jpermb) {
+    static_assert(NG == 1 || NG == 4, "one group of four waves, or one per segment");
     const int b = blockIdx.y;
     int* rot = rotb + static_cast<int64_t>(b) * max_sweeps;
     if (sweep > 0 && rot[sweep - 1] == 0) return;     // converged in an earlier sweep
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int tid = threadIdx.x & (JT - 1);           // thread of its group
+    const int lane = threadIdx.x & 63;
+    const int gwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = gwave & 3;                       // wave of its group
+    const int grp = gwave >> 2;
     int h = blockIdx.x;
     if (skip_dummy) {
         // the padding block nb - 1 holds no columns: its pair is not launched
@@ -291,24 +419,28 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
     const int bj = ring_slot(nb - 1 - h, step, nb);
     const float* Xt = Xtb + static_cast<int64_t>(b) * strideX;
 
-    // one 64 x 65 fp64 LDS buffer, reused phase by phase: the Gram's staged fp32
-    // row chunks, then the Gram, then the inner sweep's exchange arrays, then the
-    // fp32 Theta and row chunks of the rotation
-    __shared__ double G[JW][PD];
+    __shared__ __attribute__((aligned(16))) unsigned char smem[NG * kPairLds];
+    double (*G)[PD] = reinterpret_cast<double (*)[PD]>(smem);
     double (*regB)[PD] = G;
     __shared__ int col[JW];
+    __shared__ int sum_s;
 
-    if (tid < JW) {
+    if (threadIdx.x < JW) {
         // logical column c of the sweep's order -> stored column jperm[c]
         const int blk = (tid < JB) ? bi : bj;
         const int c = blk * JB + (tid & (JB - 1));
         col[tid] = (c < k) ? jpermb[static_cast<int64_t>(b) * k + c] : -1;
+        if (tid == 0) sum_s = 0;
     }
     __syncthreads();
 
-    unsigned char* lds = reinterpret_cast<unsigned char*>(&G[0][0]);
-    static_assert(2 * kChunkBytes <= JW * PD * static_cast<int>(sizeof(double)), "two plane chunks fit the buffer");
+    unsigned char* lds = smem + grp * kPairLds;
     f32x4 pre0, pre1;
+    const int nchunk = (k + PC - 1) / PC;
+    // this group's chunks, and the loop length common to all groups
+    const int ch0 = NG == 1 ? 0 : seg_begin(nchunk, grp);
+    const int nch = NG == 1 ? nchunk : seg_begin(nchunk, grp + 1) - ch0;
+    const int nit = NG == 1 ? nchunk : (nchunk + 3) / 4;
 
     // ---- 1. Gram of the pair's columns on the bf16 matrix cores: every
     //         32-row chunk of the 64 columns is split exactly into three bf16
@@ -323,63 +455,78 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
     //         (0, 3), (1, 3), so a wave reads the fragments of at most three
     //         16-column blocks.
     {
-        f64x4 acc[3];
+        f64x4 acc[3], tot[3];
 #pragma unroll
-        for (int x = 0; x < 3; ++x) acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
-        const int nchunk = (k + PC - 1) / PC;
-        pair_fetch(Xt, k, col, tid, 0, pre0, pre1);
-        pair_stash(lds, 0, tid, pre0, pre1);
+        for (int x = 0; x < 3; ++x) acc[x] = tot[x] = f64x4{0.0, 0.0, 0.0, 0.0};
+        if (nch > 0) {
+            pair_fetch(Xt, k, col, tid, ch0 * PC, pre0, pre1);
+            pair_stash(lds, 0, tid, pre0, pre1);
+        }
         __syncthreads();
         const bool diag = wave < 2;
         const int a0 = (wave == 1) ? 2 : 0, a1 = a0 + 1, bb = wave;     // bb: third block of waves 2, 3
-        for (int ch = 0; ch < nchunk; ++ch) {
-            const int s = ch & 1;
-            if (ch + 1 < nchunk) pair_fetch(Xt, k, col, tid, (ch + 1) * PC, pre0, pre1);
-            bf16x8 f0[3], f1[3];
+        for (int it = 0; it < nit; ++it) {
+            const int s = it & 1;
+            if (it + 1 < nch) pair_fetch(Xt, k, col, tid, (ch0 + it + 1) * PC, pre0, pre1);
+            if (NG == 1 || it < nch) {
+                bf16x8 f0[3], f1[3];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                f0[p] = gram_frag(lds, s, p, a0, lane);
-                f1[p] = gram_frag(lds, s, p, a1, lane);
-            }
-            if (diag) {
-                f32x4 part[3];
-#pragma unroll
-                for (int x = 0; x < 3; ++x) part[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    const int pa = kPlanePairs[q][0], pb = kPlanePairs[q][1];
-                    part[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0[pa], f0[pb], part[0], 0, 0, 0);
-                    part[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0[pa], f1[pb], part[1], 0, 0, 0);
-                    part[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[pa], f1[pb], part[2], 0, 0, 0);
+                for (int p = 0; p < 3; ++p) {
+                    f0[p] = gram_frag(lds, s, p, a0, lane);
+                    f1[p] = gram_frag(lds, s, p, a1, lane);
                 }
+                if (diag) {
+                    f32x4 part[3];
 #pragma unroll
-                for (int x = 0; x < 3; ++x)
+                    for (int x = 0; x < 3; ++x) part[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[x][v] += static_cast<double>(part[x][v]);
-            } else {
-                bf16x8 f2[3];
+                    for (int q = 0; q < 6; ++q) {
+                        const int pa = kPlanePairs[q][0], pb = kPlanePairs[q][1];
+                        part[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0[pa], f0[pb], part[0], 0, 0, 0);
+                        part[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0[pa], f1[pb], part[1], 0, 0, 0);
+                        part[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[pa], f1[pb], part[2], 0, 0, 0);
+                    }
 #pragma unroll
-                for (int p = 0; p < 3; ++p) f2[p] = gram_frag(lds, s, p, bb, lane);
-                f32x4 part[2];
+                    for (int x = 0; x < 3; ++x)
 #pragma unroll
-                for (int x = 0; x < 2; ++x) part[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                        for (int v = 0; v < 4; ++v) acc[x][v] += static_cast<double>(part[x][v]);
+                } else {
+                    bf16x8 f2[3];
 #pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    const int pa = kPlanePairs[q][0], pb = kPlanePairs[q][1];
-                    part[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0[pa], f2[pb], part[0], 0, 0, 0);
-                    part[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[pa], f2[pb], part[1], 0, 0, 0);
+                    for (int p = 0; p < 3; ++p) f2[p] = gram_frag(lds, s, p, bb, lane);
+                    f32x4 part[2];
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) part[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) {
+                        const int pa = kPlanePairs[q][0], pb = kPlanePairs[q][1];
+                        part[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0[pa], f2[pb], part[0], 0, 0, 0);
+                        part[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[pa], f2[pb], part[1], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[x][v] += static_cast<double>(part[x][v]);
                 }
-#pragma unroll
-                for (int x = 0; x < 2; ++x)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[x][v] += static_cast<double>(part[x][v]);
             }
-            if (ch + 1 < nchunk) pair_stash(lds, s ^ 1, tid, pre0, pre1);
+            if constexpr (NG == 1) {
+                // end of a segment: add its sum to the total
+                const int e = it + 1;
+                if (e == seg_begin(nchunk, 1) || e == seg_begin(nchunk, 2) || e == seg_begin(nchunk, 3) || e == nchunk) {
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) {
+                        tot[x] += acc[x];
+                        acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
+                    }
+                }
+            }
+            if (it + 1 < nch) pair_stash(lds, s ^ 1, tid, pre0, pre1);
             __syncthreads();
         }
         // 16 x 16 block layout: lane holds column (lane & 15); accumulator
         // register v holds row 4 (lane >> 4) + v. The planes are dead: the
         // last barrier above ends every read of them.
+        double (*Gp)[PD] = reinterpret_cast<double (*)[PD]>(lds);
         const int ntile = diag ? 3 : 2;
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
@@ -390,12 +537,23 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
                 for (int v = 0; v < 4; ++v) {
                     const int i = 16 * ti + 4 * (lane >> 4) + v;
                     const int j = 16 * tj + (lane & 15);
-                    G[i][j] = acc[x][v];
-                    G[j][i] = acc[x][v];
+                    const double g = NG == 1 ? tot[x][v] : acc[x][v];
+                    Gp[i][j] = g;
+                    Gp[j][i] = g;
                 }
             }
         }
         __syncthreads();
+        if constexpr (NG == 4) {
+            const double (*G1)[PD] = reinterpret_cast<const double (*)[PD]>(smem + kPairLds);
+            const double (*G2)[PD] = reinterpret_cast<const double (*)[PD]>(smem + 2 * kPairLds);
+            const double (*G3)[PD] = reinterpret_cast<const double (*)[PD]>(smem + 3 * kPairLds);
+            for (int idx = threadIdx.x; idx < JW * JW; idx += JT * NG) {
+                const int i = idx >> 6, j = idx & 63;
+                G[i][j] = ((G[i][j] + G1[i][j]) + G2[i][j]) + G3[i][j];
+            }
+            __syncthreads();
+        }
     }
 
     // ---- 2. convergence test: every column pair orthogonal to the tolerance?
@@ -403,22 +561,70 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
     //         zero column never counts, a pair with a NaN or Inf entry always
     //         does (non-finite input must not pass as converged: such a matrix
     //         runs every sweep and reports the sweep limit)
+    // The same pass forms the angles E of the joint rotation (entries below the
+    // tolerance whose angle is large, i.e. columns of nearly equal norm, stay
+    // unrotated) and their squares' sum, in whole units of 2^-24 so that the
+    // sum does not depend on its order.
+    bool small, tiny;
+    float ev[16 / NG];
     {
         const double tol2 = tol * tol;
-        int need = 0;
-        for (int idx = tid; idx < JW * JW; idx += JT) {
-            const int p = idx / JW, q = idx % JW;
+        int need = 0, big = 0, fsum = 0;
+#pragma unroll
+        for (int e = 0; e < 16 / NG; ++e) {
+            const int idx = static_cast<int>(threadIdx.x) + e * JT * NG;
+            const int p = idx >> 6, q = idx & 63;
+            ev[e] = 0.0f;
             if (q > p) {
-                const double dd = G[p][p] * G[q][q];
+                const double a = G[p][p], c = G[q][q];
+                const double dd = a * c;
                 const double gpq = G[p][q];
-                if (dd != 0.0 && (!(dd <= DBL_MAX) || !(gpq * gpq <= tol2 * dd))) need = 1;
+                if (dd != 0.0) {
+                    const bool ok = dd <= DBL_MAX && gpq * gpq <= tol2 * dd;
+                    if (!ok) need = 1;
+                    const double d = c - a;
+                    const bool fits = fabs(gpq) <= static_cast<double>(kSmallAngle) * fabs(d);
+                    if (!fits) {
+                        if (!ok) big = 1;
+                    } else if (gpq != 0.0) {
+                        if (!(fabs(d) > 1e-30 && fabs(d) < 1e30)) {
+                            big = 1;
+                        } else {
+                            ev[e] = static_cast<float>(gpq) * __builtin_amdgcn_rcpf(static_cast<float>(d));
+                            fsum += static_cast<int>(ev[e] * ev[e] * 16777216.0f);
+                        }
+                    }
+                }
             }
         }
         need = __syncthreads_or(need);
-        if (tid == 0 && need) atomicAdd(&rot[sweep], 1);
+        if (threadIdx.x == 0 && need) atomicAdd(&rot[sweep], 1);
         if (!need) return;
+        for (int o = 32; o > 0; o >>= 1) fsum += __shfl_xor(fsum, o);
+        if (lane == 0 && fsum != 0) atomicAdd(&sum_s, fsum);
+        big = __syncthreads_or(big);
+        const int total = sum_s;
+        small = !big && total <= static_cast<int>(kSmallSum * 16777216.0f);
+        tiny = total <= static_cast<int>(kTinySum * 16777216.0f);
     }
 
+    if (small) {
+        float (*E)[SP] = reinterpret_cast<float (*)[SP]>(smem);
+#pragma unroll
+        for (int e = 0; e < 16 / NG; ++e) {
+            const int idx = static_cast<int>(threadIdx.x) + e * JT * NG;
+            const int p = idx >> 6, q = idx & 63;
+            if (q >= p) {
+                E[p][q] = ev[e];
+                E[q][p] = (q > p) ? -ev[e] : 0.0f;
+            }
+        }
+        __syncthreads();
+        small_angle_theta<4 / NG>(smem, wave, NG == 1 ? 0 : grp, lane, tiny);
+    } else if (NG > 1 && grp > 0) {
+        // the inner sweep is the first group's; the others keep its barriers
+        for (int i = 0; i < 3 + kInnerSweeps * JW; ++i) __syncthreads();
+    } else
     // ---- 3. reduce the 64 x 64 Gram by one sweep of two-sided Jacobi, held
     //         in registers: lane x holds row x, wave w the columns
     //         16 w .. 16 w + 15 of it and of the accumulated rotation Theta.
@@ -432,8 +638,7 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
     //         its off-diagonal entry is read back from the holder each round.
     {
         double* Dv = &regB[0][0];                  // [2][64]: diagonal, ping-pong by round
-        jreal* CSw = reinterpret_cast<jreal*>(Dv + 2 * JW);   // [4 waves][64][2]: (c, s) by first slot, wave-private
-        jreal* Band = CSw + 4 * JW * 2;            // [2][4][16][16]: rows whose (x, x+1) entry a wave holds
+        jreal* Band = reinterpret_cast<jreal*>(Dv + 2 * JW);   // [2][4][16][16]: rows whose (x, x+1) entry a wave holds
         jreal* Halo = Band + 2 * 4 * 16 * 16;      // [4 waves][4][64]: edge columns (G left/right, Theta left/right)
         const int x = lane;
         const int c0 = 16 * wave;
@@ -490,15 +695,11 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
                 jreal cf = 1.0f, sf = 0.0f;
                 if (g * g > 1e-30 * (a * b)) rotation(a, b, gf, cf, sf);
                 // rotated slot p' = c p - s q goes to slot q, q' = s p + c q to slot p
-                if (x == p) {
-                    if ((p >> 4) == wave) {
-                        const double cr = cf, sr = sf;
-                        const double cs2 = 2.0 * cr * sr * g;
-                        Dn[p] = sr * sr * a + cs2 + cr * cr * b;
-                        Dn[q] = cr * cr * a - cs2 + sr * sr * b;
-                    }
-                    CSw[(wave * JW + p) * 2 + 0] = cf;
-                    CSw[(wave * JW + p) * 2 + 1] = sf;
+                if (x == p && (p >> 4) == wave) {
+                    const double cr = cf, sr = sf;
+                    const double cs2 = 2.0 * cr * sr * g;
+                    Dn[p] = sr * sr * a + cs2 + cr * cr * b;
+                    Dn[q] = cr * cr * a - cs2 + sr * sr * b;
                 }
                 c = cf;
                 sg = (x == p) ? sf : -sf;
@@ -518,16 +719,16 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
                 hgL = rotate_odd(hgL, sg, cn, cp);
                 hgR = rotate_odd(hgR, sg, cn, cp);
             }
-            // (c, s) of this wave's column pairs, published by their first rows
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const jreal* cw = CSw + wave * JW * 2;
+            // (c, s) of a column pair: in the lane of its first row (c there is the
+            // rotation's c, sg its s), read into scalar registers; an idle row is
+            // no pair's first
+            auto pair_c = [&](int slot) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), slot)); };
+            auto pair_s = [&](int slot) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sg), slot)); };
             // columns: new col p = s col_p + c col_q, new col q = c col_p - s col_q
             if (!par) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const jreal cc = cw[(c0 + 2 * i) * 2 + 0], ss = cw[(c0 + 2 * i) * 2 + 1];
+                    const jreal cc = pair_c(c0 + 2 * i), ss = pair_s(c0 + 2 * i);
                     const jreal g0 = gv[2 * i], g1 = gv[2 * i + 1];
                     gv[2 * i] = ss * g0 + cc * g1;
                     gv[2 * i + 1] = cc * g0 - ss * g1;
@@ -538,7 +739,7 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
             } else {
 #pragma unroll
                 for (int i = 0; i < 7; ++i) {
-                    const jreal cc = cw[(c0 + 2 * i + 1) * 2 + 0], ss = cw[(c0 + 2 * i + 1) * 2 + 1];
+                    const jreal cc = pair_c(c0 + 2 * i + 1), ss = pair_s(c0 + 2 * i + 1);
                     const jreal g0 = gv[2 * i + 1], g1 = gv[2 * i + 2];
                     gv[2 * i + 1] = ss * g0 + cc * g1;
                     gv[2 * i + 2] = cc * g0 - ss * g1;
@@ -547,12 +748,12 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
                     tv[2 * i + 2] = cc * t0 - ss * t1;
                 }
                 if (wave > 0) {      // pair (16 w - 1, 16 w): this wave keeps the second slot
-                    const jreal cc = cw[(c0 - 1) * 2 + 0], ss = cw[(c0 - 1) * 2 + 1];
+                    const jreal cc = pair_c(c0 - 1), ss = pair_s(c0 - 1);
                     gv[0] = cc * hgL - ss * gv[0];
                     tv[0] = cc * htL - ss * tv[0];
                 }
                 if (wave < 3) {      // pair (16 w + 15, 16 w + 16): this wave keeps the first slot
-                    const jreal cc = cw[(c0 + 15) * 2 + 0], ss = cw[(c0 + 15) * 2 + 1];
+                    const jreal cc = pair_c(c0 + 15), ss = pair_s(c0 + 15);
                     gv[15] = ss * gv[15] + cc * hgR;
                     tv[15] = ss * tv[15] + cc * htR;
                 }
@@ -563,9 +764,9 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
                 const int jj = x + 1 - c0;
                 const int np = (par ^ 1) ? ((x & 1) ? x : -1) : ((x & 1) ? -1 : x);   // x first of a next pair?
                 if (np >= 0 && x + 1 < JW && jj >= 0 && jj < 16) {
-                    jreal* row = Bn + (wave * 16 + jj) * 16;
+                    f32x4* row = reinterpret_cast<f32x4*>(Bn + (wave * 16 + jj) * 16);
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) row[j] = gv[j];
+                    for (int j = 0; j < 4; ++j) row[j] = f32x4{gv[4 * j], gv[4 * j + 1], gv[4 * j + 2], gv[4 * j + 3]};
                 }
                 if (!par) {
                     Halo[(wave * 4 + 0) * JW + x] = gv[0];
@@ -601,7 +802,7 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
     //         consecutive rows of one column per tile.
     {
         const int tm = wave >> 1, tn = wave & 1;
-        const float (*Tf)[PD] = reinterpret_cast<const float (*)[PD]>(&G[0][0]);   // Theta[w][c], fp32
+        const float (*Tf)[PD] = reinterpret_cast<const float (*)[PD]>(smem);   // Theta[w][c], fp32
         bf16x8 bq[2][2][3];   // [column tile][K step of 32][plane]
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct)
@@ -619,47 +820,50 @@ __global__ __launch_bounds__(JT, 4) void jacobi_pair_kernel(float* Xtb, int k, i
             }
         __syncthreads();                       // the Y_P planes overwrite Theta
         float* Y = Xtb + static_cast<int64_t>(b) * strideX;
-        const int nch = (k + PC - 1) / PC;
-        pair_fetch(Y, k, col, tid, 0, pre0, pre1);
-        pair_stash(lds, 0, tid, pre0, pre1);
+        if (nch > 0) {
+            pair_fetch(Y, k, col, tid, ch0 * PC, pre0, pre1);
+            pair_stash(lds, 0, tid, pre0, pre1);
+        }
         __syncthreads();
         const int cst[2] = {col[32 * tn + (lane & 15)], col[32 * tn + 16 + (lane & 15)]};
         const bool vec4 = (k & 3) == 0;
-        for (int ch = 0; ch < nch; ++ch) {
-            const int s = ch & 1;
-            const int r0 = ch * PC;
-            if (ch + 1 < nch) pair_fetch(Y, k, col, tid, r0 + PC, pre0, pre1);
-            f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+        for (int it = 0; it < nit; ++it) {
+            const int s = it & 1;
+            const int r0 = (ch0 + it) * PC;
+            if (it + 1 < nch) pair_fetch(Y, k, col, tid, r0 + PC, pre0, pre1);
+            if (NG == 1 || it < nch) {
+                f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                bf16x8 af[3];
+                for (int ks = 0; ks < 2; ++ks) {
+                    bf16x8 af[3];
 #pragma unroll
-                for (int p = 0; p < 3; ++p) af[p] = apply_frag(lds, s, p, tm, ks, lane);
+                    for (int p = 0; p < 3; ++p) af[p] = apply_frag(lds, s, p, tm, ks, lane);
 #pragma unroll
-                for (int q = 0; q < 6; ++q)
+                    for (int q = 0; q < 6; ++q)
 #pragma unroll
-                    for (int ct = 0; ct < 2; ++ct)
-                        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[kPlanePairs[q][0]],
-                                                                          bq[ct][ks][kPlanePairs[q][1]], acc[ct], 0,
-                                                                          0, 0);
-            }
-            // rows r0 + 16 tm + 4 (lane >> 4) + v of column cst[ct]
-            const int rr = r0 + 16 * tm + 4 * (lane >> 4);
+                        for (int ct = 0; ct < 2; ++ct)
+                            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[kPlanePairs[q][0]],
+                                                                              bq[ct][ks][kPlanePairs[q][1]], acc[ct],
+                                                                              0, 0, 0);
+                }
+                // rows r0 + 16 tm + 4 (lane >> 4) + v of column cst[ct]
+                const int rr = r0 + 16 * tm + 4 * (lane >> 4);
 #pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-                const int c = cst[ct];
-                if (c >= 0) {
-                    float* dst = Y + static_cast<int64_t>(c) * k + rr;
-                    if (vec4 && rr + 4 <= k) {
-                        *reinterpret_cast<f32x4*>(dst) = acc[ct];
-                    } else {
+                for (int ct = 0; ct < 2; ++ct) {
+                    const int c = cst[ct];
+                    if (c >= 0) {
+                        float* dst = Y + static_cast<int64_t>(c) * k + rr;
+                        if (vec4 && rr + 4 <= k) {
+                            *reinterpret_cast<f32x4*>(dst) = acc[ct];
+                        } else {
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (rr + v < k) dst[v] = acc[ct][v];
+                            for (int v = 0; v < 4; ++v)
+                                if (rr + v < k) dst[v] = acc[ct][v];
+                        }
                     }
                 }
             }
-            if (ch + 1 < nch) pair_stash(lds, s ^ 1, tid, pre0, pre1);
+            if (it + 1 < nch) pair_stash(lds, s ^ 1, tid, pre0, pre1);
             __syncthreads();
         }
     }
@@ -895,8 +1099,14 @@ hipError_t launch_jacobi_step(float* Yt, int k, int64_t strideX, int nblocks, in
     // an odd number of real blocks (at least 3) leaves one padding block
     const int nreal = (k + JB - 1) / JB;
     const int skip_dummy = (nblocks > nreal && nreal >= 3) ? 1 : 0;
-    hipLaunchKernelGGL(jacobi_pair_kernel, dim3(nblocks / 2 - skip_dummy, batch), dim3(JT), 0, stream, Yt, k,
-                       strideX, nblocks, step, sweep, rot, max_sweeps, tol, skip_dummy, jperm);
+    const int pairs = nblocks / 2 - skip_dummy;
+    // at most one workgroup per CU: four groups of waves each
+    if (static_cast<int64_t>(pairs) * batch <= kPairWideMax)
+        hipLaunchKernelGGL(jacobi_pair_kernel<4>, dim3(pairs, batch), dim3(4 * JT), 0, stream, Yt, k, strideX, nblocks,
+                           step, sweep, rot, max_sweeps, tol, skip_dummy, jperm);
+    else
+        hipLaunchKernelGGL(jacobi_pair_kernel<1>, dim3(pairs, batch), dim3(JT), 0, stream, Yt, k, strideX, nblocks,
+                           step, sweep, rot, max_sweeps, tol, skip_dummy, jperm);
     return hipGetLastError();
 }
 
