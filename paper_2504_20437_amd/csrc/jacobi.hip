@@ -23,9 +23,8 @@
 //   3. if every rotation the Gram asks for is small, takes them all at once
 //      (Theta = polar factor of I + E, four small matrix-core products), else
 //      reduces the small Gram by one sweep of two-sided Jacobi held in
-//      registers (fp32 entries, fp64 diagonal and angles; odd-even ordering,
-//      64 rounds of up to 32 disjoint rotations, accumulating the rotation
-//      Theta), and
+//      registers (fp32 entries, fp64 diagonal and angles; 63 rounds of 32
+//      disjoint rotations, accumulating the rotation Theta), and
 //   4. applies Theta to the pair's 64 columns of Y on the bf16 matrix cores,
 //      Theta and the 32-row chunks of Y split into three planes as in 1.
 // A launch of few workgroups runs them with four groups of four waves, the
@@ -50,10 +49,6 @@ namespace {
 
 constexpr int JB = kJacobiBlock;   // columns per block
 constexpr int JW = 2 * JB;         // columns per pair (64)
-#ifndef GALORE_JAC_INNER
-#define GALORE_JAC_INNER 1
-#endif
-constexpr int kInnerSweeps = GALORE_JAC_INNER;   // inner sweeps of a pair's 64 x 64 Gram per visit
 constexpr int JT = 256;            // threads (4 waves)
 constexpr int PD = JW + 1;         // padded LDS row
 constexpr int kPairWideMax = 256;  // workgroups up to which a step's launch takes the wide form (the CUs)
@@ -135,40 +130,6 @@ __device__ __forceinline__ void rotation(double a, double b, float g, float& c, 
     s = c * tf;
 }
 
-// Cross-lane moves of an fp32 value within a wave (DPP, no LDS traffic).
-// dpp_swap_pairs: lane x receives lane x ^ 1. dpp_from_next / dpp_from_prev:
-// lane x receives lane x + 1 / x - 1 (whole-wave shifts); lanes without a
-// source (63 / 0) read 0. A zero old value and bound_ctrl let the compiler
-// fold the lane move into the multiply that uses it.
-__device__ __forceinline__ float dpp_swap_pairs(float v) {
-    const int i = __float_as_int(v);
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float dpp_from_next(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float dpp_from_prev(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-// odd rounds: an odd lane's partner row is lane x + 1, an even lane's x - 1;
-// with cn = c on odd lanes (0 on even ones) and cp the other way round, the
-// partner term is fma(v[x - 1], cp, cn * v[x + 1]). Both lane moves are folded
-// into the two instructions that use them (the compiler's own DPP folding
-// leaves one or both as separate moves here: five instructions per value
-// instead of three); lanes 0 and 63 read 0 for their missing neighbour, as
-// the moves above do. The leading s_nop gives the two wait states a DPP read
-// needs after a VALU write of its source (not checked by the compiler inside
-// inline assembly).
-__device__ __forceinline__ float rotate_odd(float v, float sg, float cn, float cp) {
-    float t;
-    asm("s_nop 1\n\t"
-        "v_mul_f32_dpp %0, %1, %2 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        "v_fmac_f32_dpp %0, %1, %3 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-        : "=&v"(t)
-        : "v"(v), "v"(cn), "v"(cp));
-    return fmaf(sg, v, t);
-}
-
 // ---- bf16 planes of the pair's columns (Gram and rotation phases) ----------
 // A 32-row chunk of the pair's 64 columns is held in LDS as three bf16 planes
 // (h, m, l with x = h + m + l exactly: each plane takes the leading 8
@@ -198,37 +159,33 @@ __device__ __forceinline__ void split8(f32x4 a, f32x4 b, bf16x8& h, bf16x8& m, b
         const unsigned v0 = __float_as_uint(r0), v1 = __float_as_uint(r1);
         const float q0 = r0 - __uint_as_float(v0 & 0xffff0000u);
         const float q1 = r1 - __uint_as_float(v1 & 0xffff0000u);
-        ph[i] = (u0 >> 16) | (u1 & 0xffff0000u);
-        pm[i] = (v0 >> 16) | (v1 & 0xffff0000u);
-        pl[i] = (__float_as_uint(q0) >> 16) | (__float_as_uint(q1) & 0xffff0000u);
+        // the upper halves of two words in one
+        ph[i] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+        pm[i] = __builtin_amdgcn_perm(v1, v0, 0x07060302u);
+        pl[i] = __builtin_amdgcn_perm(__float_as_uint(q1), __float_as_uint(q0), 0x07060302u);
     }
     h = __builtin_bit_cast(bf16x8, ph);
     m = __builtin_bit_cast(bf16x8, pm);
     l = __builtin_bit_cast(bf16x8, pl);
 }
 
-// thread t loads rows r0 + 8 (t & 3) .. + 7 of pair column t >> 2 (zeros past
-// k and for padding columns)
-__device__ __forceinline__ void pair_fetch(const float* X, int k, const int* col, int tid, int r0, f32x4& a,
-                                           f32x4& b) {
-    const int c = col[tid >> 2];
-    const int rr = r0 + 8 * (tid & 3);
-    const int64_t base = static_cast<int64_t>(c) * k + rr;
-    if (c >= 0 && (k & 3) == 0 && rr + 8 <= k) {
-        a = *reinterpret_cast<const f32x4*>(X + base);
-        b = *reinterpret_cast<const f32x4*>(X + base + 4);
-    } else {
+struct Rows8 {
+    f32x4 a, b;
+};
+// entries 0 .. 7 of src (zeros past `left` of them); vec: 16-byte aligned
+__device__ __forceinline__ Rows8 pair_fetch(const float* src, int left, bool vec) {
+    if (vec && left >= 8)
+        return Rows8{*reinterpret_cast<const f32x4*>(src), *reinterpret_cast<const f32x4*>(src + 4)};
+    float v[8];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            a[v] = (c >= 0 && rr + v < k) ? X[base + v] : 0.0f;
-            b[v] = (c >= 0 && rr + 4 + v < k) ? X[base + 4 + v] : 0.0f;
-        }
-    }
+    for (int e = 0; e < 8; ++e) v[e] = (e < left) ? src[e] : 0.0f;
+    return Rows8{f32x4{v[0], v[1], v[2], v[3]}, f32x4{v[4], v[5], v[6], v[7]}};
 }
 
-__device__ __forceinline__ void pair_stash(unsigned char* lds, int s, int tid, f32x4 a, f32x4 b) {
+// thread t stages rows 8 (t & 3) .. + 7 of the chunk of pair column t >> 2
+__device__ __forceinline__ void pair_stash(unsigned char* lds, int s, int tid, Rows8 r) {
     bf16x8 h, m, l;
-    split8(a, b, h, m, l);
+    split8(r.a, r.b, h, m, l);
     const int c = tid >> 2, o = tid & 3;
     unsigned char* dst = lds + s * kChunkBytes + c * 64 + 16 * (o ^ ((c >> 2) & 3));
     *reinterpret_cast<bf16x8*>(dst) = h;
@@ -384,6 +341,319 @@ __device__ __forceinline__ void small_angle_theta(unsigned char* smem, int wr, i
     __syncthreads();
 }
 
+// v of lane x ^ M within each 16 lanes (M = 1, 2: quad permutations)
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+    static_assert(M == 1 || M == 2, "quad permutations");
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), M == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+}
+template <int M>
+__device__ __forceinline__ int lane_xor(int v) {
+    return __builtin_amdgcn_mov_dpp(v, M == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true);
+}
+template <int M>
+__device__ __forceinline__ double lane_xor(double v) {
+    const int64_t u = __double_as_longlong(v);
+    const uint32_t lo = lane_xor<M>(static_cast<int>(u)), hi = lane_xor<M>(static_cast<int>(u >> 32));
+    return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+// v of the lane whose byte address (4 times its number) is a
+__device__ __forceinline__ int lane_at(int a, int v) { return __builtin_amdgcn_ds_bpermute(a, v); }
+__device__ __forceinline__ float lane_at(int a, float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(a, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_at(int a, double v) {
+    const int64_t u = __double_as_longlong(v);
+    const uint32_t lo = lane_at(a, static_cast<int>(u)), hi = lane_at(a, static_cast<int>(u >> 32));
+    return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
+// One sweep of two-sided Jacobi on the 64 x 64 Gram (upper triangle, fp64, in
+// LDS on entry), held in registers; on exit the accumulated rotation Theta (fp32, row pitch
+// PD) is in LDS. All four waves of a group; ACTIVE = false runs the barriers
+// alone.
+//
+// The 64 columns sit in 32 positions of two, A and B; a round rotates the 32
+// pairs (A_p, B_p). Wave w holds positions 8 w .. 8 w + 7; lane x + 32 h (x <
+// 32) the rows of A_x and B_x of the Gram, and rows x and 32 + x of Theta, at
+// the eight columns of positions 8 w + 4 h .. + 3: both rows and both columns
+// of a rotation are in one lane, so a round's rotations are 96 multiply-adds
+// a lane with no lane moves. The pair's diagonal entries are carried along
+// exactly (2 x 2 formulas, fp64); its off-diagonal entry is read from its
+// holder (one LDS word, one barrier a round).
+// Between rounds the B side is permuted by p -> p ^ m: m = 1, 2 are register
+// renames for the columns and quad permutations for the rows; every fourth
+// round m = 7, 15 or 16 goes through LDS. m steps through a Gray code of the
+// basis {1, 2, 7, 15, 16}, so 32 rounds meet every A with every B. Then A and
+// B are paired anew across bit 4 (A_p with A_p^16, B_p with B_p^16) and 16
+// rounds do the same within the halves, and so on down: 32 + 16 + 8 + 4 + 2 +
+// 1 = 63 rounds, in which every pair of columns meets once.
+// (One row a lane, 64 odd-even rounds with a lane move per value and round,
+// took 46 us of the visit in a workgroup alone on its CU; this form 30 us.)
+constexpr int kSweepScratch = JW * SP * static_cast<int>(sizeof(float));   // past Theta and the exchanged columns
+static_assert(JW * PD * static_cast<int>(sizeof(float)) <= kSweepScratch && 32 * 32 * 16 <= kSweepScratch &&
+                  kSweepScratch + 2048 <= kPairLds, "sweep scratch");
+
+template <bool ACTIVE>
+__device__ __forceinline__ void inner_sweep(unsigned char* smem, int wave, int lane) {
+    const double (*G)[PD] = reinterpret_cast<const double (*)[PD]>(smem);
+    f32x4 (*Xb)[32] = reinterpret_cast<f32x4 (*)[32]>(smem);                          // exchanged columns by position
+    float (*gx)[32] = reinterpret_cast<float (*)[32]>(smem + kSweepScratch);          // [2] off-diagonals, ping-pong
+    float2 (*cs)[32] = reinterpret_cast<float2 (*)[32]>(smem + kSweepScratch + 256);  // [4 waves] (c, s), wave-private
+    int (*ids)[32] = reinterpret_cast<int (*)[32]>(smem + kSweepScratch + 1280);      // [2] columns held by A and B
+    const int x = lane & 31, h = lane >> 5;
+    const int p0 = 8 * wave + 4 * h;             // this lane's first position
+    const bool holder = (x >> 2) == (p0 >> 2);   // position x's columns are this lane's
+    float gAA[4], gAB[4], gBA[4], gBB[4];        // Gram rows A_x, B_x at columns A_p, B_p of position p0 + j
+    float t0A[4], t0B[4], t1A[4], t1B[4];        // Theta rows x, 32 + x
+    double da = 0.0, db = 0.0;                   // the diagonal entries of A_x and B_x
+    int ia = x, ib = 32 + x;                     // the columns they are
+    if constexpr (ACTIVE) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int p = p0 + j;
+            const int lo = min(x, p), hi = max(x, p);
+            gAA[j] = static_cast<float>(G[lo][hi]);
+            gAB[j] = static_cast<float>(G[x][32 + p]);
+            gBA[j] = static_cast<float>(G[p][32 + x]);
+            gBB[j] = static_cast<float>(G[32 + lo][32 + hi]);
+            t0A[j] = t1B[j] = (x == p) ? 1.0f : 0.0f;
+            t0B[j] = t1A[j] = 0.0f;
+        }
+        da = G[x][x];
+        db = G[32 + x][32 + x];
+    }
+    __syncthreads();                             // the exchange arrays overwrite the Gram
+    int buf = 0;
+    float g = 0.0f;                              // the coming round's off-diagonal of position x
+    float cj[4], sj[4];                          // the round's rotations of the lane's positions
+    // p' = c p - s q, q' = s p + c q
+    auto turn2 = [](float& p, float& q, float cc, float ss) {
+        const float u = cc * p - ss * q;
+        q = ss * p + cc * q;
+        p = u;
+    };
+    // position x's next off-diagonal, at the holder's column B_(x ^ M), to every wave
+    auto put = [&](auto mc) __attribute__((always_inline)) {
+        constexpr int M = decltype(mc)::value;
+        if constexpr (ACTIVE) {
+            const float v01 = (x & 1) ? gAB[1 ^ M] : gAB[M], v23 = (x & 1) ? gAB[3 ^ M] : gAB[2 ^ M];
+            if (holder) gx[buf][x] = (x & 2) ? v23 : v01;
+        }
+    };
+    auto get = [&]() __attribute__((always_inline)) {
+        __syncthreads();
+        if constexpr (ACTIVE) g = gx[buf][x];
+        buf ^= 1;
+    };
+    auto publish = [&]() __attribute__((always_inline)) {
+        put(std::integral_constant<int, 0>());
+        get();
+    };
+    // a round's rotations: the rows and the A_x row's columns first (the next
+    // off-diagonal is among them) ...
+    auto rotate_a = [&]() __attribute__((always_inline)) {
+        if constexpr (ACTIVE) {
+            const double gd = g;
+            float c, s;
+            rotation(da, db, g, c, s);
+            const bool turn = gd * gd > 1e-30 * (da * db);
+            c = turn ? c : 1.0f;
+            s = turn ? s : 0.0f;
+            if (h == 0) cs[wave][x] = make_float2(c, s);
+            // the wave's own LDS writes and reads are in order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const f32x4 q01 = *reinterpret_cast<const f32x4*>(&cs[wave][p0]);
+            const f32x4 q23 = *reinterpret_cast<const f32x4*>(&cs[wave][p0 + 2]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                turn2(gAA[j], gBA[j], c, s);
+                turn2(gAB[j], gBB[j], c, s);
+            }
+            const double cr = c, sr = s;
+            const double cs2 = 2.0 * cr * sr * gd;
+            const double na = cr * cr * da - cs2 + sr * sr * db;
+            db = sr * sr * da + cs2 + cr * cr * db;
+            da = na;
+            cj[0] = q01[0], sj[0] = q01[1], cj[1] = q01[2], sj[1] = q01[3];
+            cj[2] = q23[0], sj[2] = q23[1], cj[3] = q23[2], sj[3] = q23[3];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) turn2(gAA[j], gAB[j], cj[j], sj[j]);
+        }
+    };
+    // ... then the B_x row's and Theta's columns
+    auto rotate_b = [&]() __attribute__((always_inline)) {
+        if constexpr (ACTIVE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) turn2(gBA[j], gBB[j], cj[j], sj[j]);
+        }
+    };
+    auto rotate_t = [&]() __attribute__((always_inline)) {
+        if constexpr (ACTIVE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                turn2(t0A[j], t0B[j], cj[j], sj[j]);
+                turn2(t1A[j], t1B[j], cj[j], sj[j]);
+            }
+        }
+    };
+    auto rotate = [&]() __attribute__((always_inline)) {
+        rotate_a();
+        rotate_b();
+        rotate_t();
+    };
+    auto swap1 = [](float& u, float& v) {
+        const float w = u;
+        u = v;
+        v = w;
+    };
+    // B_p -> position p ^ M, M = 1 or 2
+    auto flip = [&](auto mc) __attribute__((always_inline)) {
+        constexpr int M = decltype(mc)::value;
+        if constexpr (ACTIVE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if ((j & M) != 0) continue;
+                swap1(gAB[j], gAB[j ^ M]);
+                swap1(gBB[j], gBB[j ^ M]);
+                swap1(t0B[j], t0B[j ^ M]);
+                swap1(t1B[j], t1B[j ^ M]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                gBA[j] = lane_xor<M>(gBA[j]);
+                gBB[j] = lane_xor<M>(gBB[j]);
+            }
+            db = lane_xor<M>(db);
+            ib = lane_xor<M>(ib);
+        }
+    };
+    // the rows of a move across positions p ^ m: `both` sides' rows change
+    // places (a new pairing), or B's alone move
+    auto move_rows = [&](int m, bool pairing) __attribute__((always_inline)) {
+        if constexpr (ACTIVE) {
+            const int src = 4 * (lane ^ m);
+            const bool up = pairing && (x & m) != 0;   // these lanes give and take A, the others B
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float va = lane_at(src, (pairing && !up) ? gBA[j] : (pairing ? gAA[j] : gBA[j]));
+                const float vb = lane_at(src, (pairing && !up) ? gBB[j] : (pairing ? gAB[j] : gBB[j]));
+                gAA[j] = up ? va : gAA[j];
+                gAB[j] = up ? vb : gAB[j];
+                gBA[j] = up ? gBA[j] : va;
+                gBB[j] = up ? gBB[j] : vb;
+            }
+            const double vd = lane_at(src, (pairing && up) ? da : db);
+            const int vi = lane_at(src, (pairing && up) ? ia : ib);
+            da = up ? vd : da;
+            ia = up ? vi : ia;
+            db = up ? db : vd;
+            ib = up ? ib : vi;
+        }
+    };
+    // a move across p ^ m, m >= 4: the columns through LDS
+    auto exchange = [&](int m, bool pairing) __attribute__((always_inline)) {
+        const bool up = pairing && (p0 & m) != 0;      // uniform over the lane's four positions
+        if constexpr (ACTIVE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                Xb[p0 + j][x] = up ? f32x4{gAA[j], gBA[j], t0A[j], t1A[j]} : f32x4{gAB[j], gBB[j], t0B[j], t1B[j]};
+        }
+        __syncthreads();
+        if constexpr (ACTIVE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 v = Xb[(p0 + j) ^ m][x];
+                gAA[j] = up ? v[0] : gAA[j];
+                gBA[j] = up ? v[1] : gBA[j];
+                t0A[j] = up ? v[2] : t0A[j];
+                t1A[j] = up ? v[3] : t1A[j];
+                gAB[j] = up ? gAB[j] : v[0];
+                gBB[j] = up ? gBB[j] : v[1];
+                t0B[j] = up ? t0B[j] : v[2];
+                t1B[j] = up ? t1B[j] : v[3];
+            }
+        }
+        move_rows(m, pairing);
+    };
+    // a new pairing across bit 2 or 1 of the position: register renames
+    auto pair_low = [&](auto mc) __attribute__((always_inline)) {
+        constexpr int M = decltype(mc)::value;
+        if constexpr (ACTIVE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if ((j & M) != 0) continue;            // B_j with A_(j + M)
+                swap1(gAB[j], gAA[j ^ M]);
+                swap1(gBB[j], gBA[j ^ M]);
+                swap1(t0B[j], t0A[j ^ M]);
+                swap1(t1B[j], t1A[j ^ M]);
+            }
+        }
+        move_rows(M, true);
+    };
+    using std::integral_constant;
+    // a round, then B_p -> position p ^ M (M = 1 or 2): the next off-diagonal
+    // is written before the rest of the round's work and read behind it
+    auto round_flip = [&](auto mc) __attribute__((always_inline)) {
+        rotate_a();
+        put(mc);
+        __builtin_amdgcn_sched_barrier(0);
+        rotate_b();
+        get();
+        __builtin_amdgcn_sched_barrier(0);
+        rotate_t();
+        flip(mc);
+    };
+    auto four_rounds = [&]() __attribute__((always_inline)) {
+        round_flip(integral_constant<int, 1>());
+        round_flip(integral_constant<int, 2>());
+        round_flip(integral_constant<int, 1>());
+        rotate();
+    };
+    publish();
+    // moves after each four rounds, a nibble each from the lowest: 7, 15, 16, or
+    // a new pairing across bit 4, 3 (value 8) or 2 (value 4); the last four
+    // rounds (positions of two bits) follow
+    constexpr uint64_t kMoves = 0x47A7F7B7F7E7F7ULL;
+    for (int i = 0; i < 14; ++i) {
+        four_rounds();
+        const int mv = static_cast<int>((kMoves >> (4 * i)) & 15);
+        if (mv == 0x7 || mv == 0xF) exchange(mv, false);
+        else if (mv == 0xE) exchange(16, false);
+        else exchange(mv == 0xB ? 16 : (mv == 0xA ? 8 : 4), true);
+        publish();
+    }
+    four_rounds();
+    pair_low(integral_constant<int, 2>());
+    publish();
+    round_flip(integral_constant<int, 1>());
+    rotate();
+    pair_low(integral_constant<int, 1>());
+    publish();
+    rotate();
+    if constexpr (ACTIVE) {
+        if (wave == 0 && h == 0) {
+            ids[0][x] = ia;
+            ids[1][x] = ib;
+        }
+    }
+    __syncthreads();
+    if constexpr (ACTIVE) {
+        float (*Tf)[PD] = reinterpret_cast<float (*)[PD]>(smem);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int ca = ids[0][p0 + j], cb = ids[1][p0 + j];
+            Tf[x][ca] = t0A[j];
+            Tf[x][cb] = t0B[j];
+            Tf[32 + x][ca] = t1A[j];
+            Tf[32 + x][cb] = t1B[j];
+        }
+    }
+    __syncthreads();
+}
+
 // Step of the block Jacobi (one workgroup per pair and matrix): Gram of the
 // pair's 64 columns, convergence test, reduction of the small Gram, rotation
 // of the columns, all in one LDS buffer per group of four waves (see above).
@@ -391,7 +661,9 @@ __device__ __forceinline__ void small_angle_theta(unsigned char* smem, int wr, i
 // launches whose workgroups do not outnumber the CUs: the chunk loops of the
 // two phases over memory wait a memory latency per chunk, which only other
 // workgroups of the CU would hide, so four groups walk a quarter of the chunks
-// each. The results are the same bits.
+// each. The results are the same bits. One 4096x11008 update (k = 1056, 16
+// workgroups a launch), per launch: 101 us with the inner sweep before and 61
+// us now, 36 us with small rotations only, 37 and 15 us where nothing rotates.
 template <int NG>
 __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(float* Xtb, int k, int64_t strideX,
                                                                                int nb, int step, int sweep, int* rotb,
@@ -421,7 +693,6 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
 
     __shared__ __attribute__((aligned(16))) unsigned char smem[NG * kPairLds];
     double (*G)[PD] = reinterpret_cast<double (*)[PD]>(smem);
-    double (*regB)[PD] = G;
     __shared__ int col[JW];
     __shared__ int sum_s;
 
@@ -435,12 +706,21 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
     __syncthreads();
 
     unsigned char* lds = smem + grp * kPairLds;
-    f32x4 pre0, pre1;
     const int nchunk = (k + PC - 1) / PC;
     // this group's chunks, and the loop length common to all groups
     const int ch0 = NG == 1 ? 0 : seg_begin(nchunk, grp);
     const int nch = NG == 1 ? nchunk : seg_begin(nchunk, grp + 1) - ch0;
     const int nit = NG == 1 ? nchunk : (nchunk + 3) / 4;
+    // this thread's column and its first row in a chunk (none for a padding column)
+    const int mycol = col[tid >> 2];
+    const int myrow = ch0 * PC + 8 * (tid & 3);
+    const int myrows = mycol >= 0 ? k - myrow : 0;   // rows from there on
+    const int64_t myoff = static_cast<int64_t>(max(mycol, 0)) * k + myrow;
+    const bool vec4 = (k & 3) == 0;
+    Rows8 pre;   // the next chunk, in flight
+    auto fetch = [&](const float* src, int it) {
+        if (it < nch) pre = pair_fetch(src + myoff + it * PC, myrows - it * PC, vec4);
+    };
 
     // ---- 1. Gram of the pair's columns on the bf16 matrix cores: every
     //         32-row chunk of the 64 columns is split exactly into three bf16
@@ -458,16 +738,14 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
         f64x4 acc[3], tot[3];
 #pragma unroll
         for (int x = 0; x < 3; ++x) acc[x] = tot[x] = f64x4{0.0, 0.0, 0.0, 0.0};
-        if (nch > 0) {
-            pair_fetch(Xt, k, col, tid, ch0 * PC, pre0, pre1);
-            pair_stash(lds, 0, tid, pre0, pre1);
-        }
+        fetch(Xt, 0);
+        if (nch > 0) pair_stash(lds, 0, tid, pre);
         __syncthreads();
         const bool diag = wave < 2;
         const int a0 = (wave == 1) ? 2 : 0, a1 = a0 + 1, bb = wave;     // bb: third block of waves 2, 3
         for (int it = 0; it < nit; ++it) {
             const int s = it & 1;
-            if (it + 1 < nch) pair_fetch(Xt, k, col, tid, (ch0 + it + 1) * PC, pre0, pre1);
+            fetch(Xt, it + 1);
             if (NG == 1 || it < nch) {
                 bf16x8 f0[3], f1[3];
 #pragma unroll
@@ -487,9 +765,7 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
                         part[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[pa], f1[pb], part[2], 0, 0, 0);
                     }
 #pragma unroll
-                    for (int x = 0; x < 3; ++x)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[x][v] += static_cast<double>(part[x][v]);
+                    for (int x = 0; x < 3; ++x) acc[x] += __builtin_convertvector(part[x], f64x4);
                 } else {
                     bf16x8 f2[3];
 #pragma unroll
@@ -504,9 +780,7 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
                         part[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1[pa], f2[pb], part[1], 0, 0, 0);
                     }
 #pragma unroll
-                    for (int x = 0; x < 2; ++x)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[x][v] += static_cast<double>(part[x][v]);
+                    for (int x = 0; x < 2; ++x) acc[x] += __builtin_convertvector(part[x], f64x4);
                 }
             }
             if constexpr (NG == 1) {
@@ -520,7 +794,7 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
                     }
                 }
             }
-            if (it + 1 < nch) pair_stash(lds, s ^ 1, tid, pre0, pre1);
+            if (it + 1 < nch) pair_stash(lds, s ^ 1, tid, pre);
             __syncthreads();
         }
         // 16 x 16 block layout: lane holds column (lane & 15); accumulator
@@ -564,18 +838,17 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
     // The same pass forms the angles E of the joint rotation (entries below the
     // tolerance whose angle is large, i.e. columns of nearly equal norm, stay
     // unrotated) and their squares' sum, in whole units of 2^-24 so that the
-    // sum does not depend on its order.
+    // sum does not depend on its order. E goes into the Gram's lower triangle,
+    // which nothing reads from here on.
     bool small, tiny;
-    float ev[16 / NG];
     {
         const double tol2 = tol * tol;
         int need = 0, big = 0, fsum = 0;
-#pragma unroll
-        for (int e = 0; e < 16 / NG; ++e) {
-            const int idx = static_cast<int>(threadIdx.x) + e * JT * NG;
+#pragma unroll 2
+        for (int idx = threadIdx.x; idx < JW * JW; idx += JT * NG) {
             const int p = idx >> 6, q = idx & 63;
-            ev[e] = 0.0f;
             if (q > p) {
+                float ev = 0.0f;
                 const double a = G[p][p], c = G[q][q];
                 const double dd = a * c;
                 const double gpq = G[p][q];
@@ -590,11 +863,12 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
                         if (!(fabs(d) > 1e-30 && fabs(d) < 1e30)) {
                             big = 1;
                         } else {
-                            ev[e] = static_cast<float>(gpq) * __builtin_amdgcn_rcpf(static_cast<float>(d));
-                            fsum += static_cast<int>(ev[e] * ev[e] * 16777216.0f);
+                            ev = static_cast<float>(gpq) * __builtin_amdgcn_rcpf(static_cast<float>(d));
+                            fsum += static_cast<int>(ev * ev * 16777216.0f);
                         }
                     }
                 }
+                G[q][p] = ev;
             }
         }
         need = __syncthreads_or(need);
@@ -610,187 +884,28 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
 
     if (small) {
         float (*E)[SP] = reinterpret_cast<float (*)[SP]>(smem);
+        float ev[16 / NG];
 #pragma unroll
         for (int e = 0; e < 16 / NG; ++e) {
             const int idx = static_cast<int>(threadIdx.x) + e * JT * NG;
             const int p = idx >> 6, q = idx & 63;
-            if (q >= p) {
-                E[p][q] = ev[e];
-                E[q][p] = (q > p) ? -ev[e] : 0.0f;
-            }
+            const float v = static_cast<float>(G[max(p, q)][min(p, q)]);
+            ev[e] = (q > p) ? v : ((q < p) ? -v : 0.0f);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 16 / NG; ++e) {
+            const int idx = static_cast<int>(threadIdx.x) + e * JT * NG;
+            E[idx >> 6][idx & 63] = ev[e];
         }
         __syncthreads();
         small_angle_theta<4 / NG>(smem, wave, NG == 1 ? 0 : grp, lane, tiny);
     } else if (NG > 1 && grp > 0) {
         // the inner sweep is the first group's; the others keep its barriers
-        for (int i = 0; i < 3 + kInnerSweeps * JW; ++i) __syncthreads();
-    } else
-    // ---- 3. reduce the 64 x 64 Gram by one sweep of two-sided Jacobi, held
-    //         in registers: lane x holds row x, wave w the columns
-    //         16 w .. 16 w + 15 of it and of the accumulated rotation Theta.
-    //         Odd-even ordering: round t pairs the slots (p, p + 1) with
-    //         p = t mod 2, t mod 2 + 2, ...; every rotation also swaps its two
-    //         slots, so that after 64 rounds every pair of columns has met once
-    //         and the slot order is reversed. Row exchanges are lane shuffles,
-    //         column exchanges register moves; the columns at a wave's slab
-    //         edges come from its neighbours (halo copies) in odd rounds. The
-    //         pair's diagonal entries are carried along exactly (2 x 2 formulas),
-    //         its off-diagonal entry is read back from the holder each round.
-    {
-        double* Dv = &regB[0][0];                  // [2][64]: diagonal, ping-pong by round
-        jreal* Band = reinterpret_cast<jreal*>(Dv + 2 * JW);   // [2][4][16][16]: rows whose (x, x+1) entry a wave holds
-        jreal* Halo = Band + 2 * 4 * 16 * 16;      // [4 waves][4][64]: edge columns (G left/right, Theta left/right)
-        const int x = lane;
-        const int c0 = 16 * wave;
-        jreal gv[16], tv[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            gv[j] = static_cast<jreal>(G[x][c0 + j]);
-            tv[j] = (x == c0 + j) ? jreal(1) : jreal(0);
-        }
-        const double dxx = G[x][x];
-        const jreal exx = (x & 1) ? jreal(0) : static_cast<jreal>(G[x][x + 1]);
-        __syncthreads();                       // the exchange arrays overwrite the Gram
-        if (wave == 0) Dv[x] = dxx;
-        // round 0 reads (x, x+1) for even x: stage it in Band[0]
-        {
-            const int jj = x + 1 - c0;
-            if (!(x & 1) && jj >= 0 && jj < 16) {
-                jreal* row = Band + ((0 * 4 + wave) * 16 + jj) * 16;
-                row[jj] = exx;
-            }
-        }
-        __syncthreads();
-        jreal hgL = 0, hgR = 0, htL = 0, htR = 0;
-        // rounds in (even, odd) pairs: the parity is a compile-time constant of
-        // each half, so the parity branches vanish and the loop-carried
-        // registers need no copies between rounds
-        auto round = [&](auto parc) {
-            constexpr int par = decltype(parc)::value;
-            const double* Dc = Dv + par * JW;
-            double* Dn = Dv + (par ^ 1) * JW;
-            const jreal* Bc = Band + par * (4 * 16 * 16);
-            jreal* Bn = Band + (par ^ 1) * (4 * 16 * 16);
-            if (par) {
-                // halo columns 16 w - 1 and 16 w + 16 as the neighbours left them
-                if (wave > 0) {
-                    hgL = Halo[((wave - 1) * 4 + 1) * JW + x];
-                    htL = Halo[((wave - 1) * 4 + 3) * JW + x];
-                }
-                if (wave < 3) {
-                    hgR = Halo[((wave + 1) * 4 + 0) * JW + x];
-                    htR = Halo[((wave + 1) * 4 + 2) * JW + x];
-                }
-            }
-            // the pair of row x and its rotation (every lane computes its own)
-            const int p = par ? ((x & 1) ? x : x - 1) : (x & ~1);
-            const bool idle = par && (x == 0 || x == JW - 1);
-            jreal c = 0, sg = 1;               // idle rows stay as they are
-            if (!idle) {
-                const int q = p + 1;
-                const int wq = q >> 4, jq = q & 15;
-                const double a = Dc[p], b = Dc[q];
-                const jreal gf = Bc[(wq * 16 + jq) * 16 + jq];
-                const double g = static_cast<double>(gf);
-                jreal cf = 1.0f, sf = 0.0f;
-                if (g * g > 1e-30 * (a * b)) rotation(a, b, gf, cf, sf);
-                // rotated slot p' = c p - s q goes to slot q, q' = s p + c q to slot p
-                if (x == p && (p >> 4) == wave) {
-                    const double cr = cf, sr = sf;
-                    const double cs2 = 2.0 * cr * sr * g;
-                    Dn[p] = sr * sr * a + cs2 + cr * cr * b;
-                    Dn[q] = cr * cr * a - cs2 + sr * sr * b;
-                }
-                c = cf;
-                sg = (x == p) ? sf : -sf;
-            } else if ((x >> 4) == wave) {
-                Dn[x] = Dc[x];
-            }
-            // rows: new row p = s row_p + c row_q, new row q = c row_p - s row_q;
-            // the partner row is lane x ^ 1 (even rounds) or x -/+ 1 (odd rounds)
-            if (!par) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) gv[j] = sg * gv[j] + c * dpp_swap_pairs(gv[j]);
-            } else {
-                const bool odd = (x & 1) != 0;
-                const jreal cn = odd ? c : jreal(0), cp = odd ? jreal(0) : c;
-#pragma unroll
-                for (int j = 0; j < 16; ++j) gv[j] = rotate_odd(gv[j], sg, cn, cp);
-                hgL = rotate_odd(hgL, sg, cn, cp);
-                hgR = rotate_odd(hgR, sg, cn, cp);
-            }
-            // (c, s) of a column pair: in the lane of its first row (c there is the
-            // rotation's c, sg its s), read into scalar registers; an idle row is
-            // no pair's first
-            auto pair_c = [&](int slot) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), slot)); };
-            auto pair_s = [&](int slot) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sg), slot)); };
-            // columns: new col p = s col_p + c col_q, new col q = c col_p - s col_q
-            if (!par) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const jreal cc = pair_c(c0 + 2 * i), ss = pair_s(c0 + 2 * i);
-                    const jreal g0 = gv[2 * i], g1 = gv[2 * i + 1];
-                    gv[2 * i] = ss * g0 + cc * g1;
-                    gv[2 * i + 1] = cc * g0 - ss * g1;
-                    const jreal t0 = tv[2 * i], t1 = tv[2 * i + 1];
-                    tv[2 * i] = ss * t0 + cc * t1;
-                    tv[2 * i + 1] = cc * t0 - ss * t1;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 7; ++i) {
-                    const jreal cc = pair_c(c0 + 2 * i + 1), ss = pair_s(c0 + 2 * i + 1);
-                    const jreal g0 = gv[2 * i + 1], g1 = gv[2 * i + 2];
-                    gv[2 * i + 1] = ss * g0 + cc * g1;
-                    gv[2 * i + 2] = cc * g0 - ss * g1;
-                    const jreal t0 = tv[2 * i + 1], t1 = tv[2 * i + 2];
-                    tv[2 * i + 1] = ss * t0 + cc * t1;
-                    tv[2 * i + 2] = cc * t0 - ss * t1;
-                }
-                if (wave > 0) {      // pair (16 w - 1, 16 w): this wave keeps the second slot
-                    const jreal cc = pair_c(c0 - 1), ss = pair_s(c0 - 1);
-                    gv[0] = cc * hgL - ss * gv[0];
-                    tv[0] = cc * htL - ss * tv[0];
-                }
-                if (wave < 3) {      // pair (16 w + 15, 16 w + 16): this wave keeps the first slot
-                    const jreal cc = pair_c(c0 + 15), ss = pair_s(c0 + 15);
-                    gv[15] = ss * gv[15] + cc * hgR;
-                    tv[15] = ss * tv[15] + cc * htR;
-                }
-            }
-            // publish for the next round: the rows whose (x, x+1) entry lies in
-            // this wave's slab, and after an even round the slab's edge columns
-            {
-                const int jj = x + 1 - c0;
-                const int np = (par ^ 1) ? ((x & 1) ? x : -1) : ((x & 1) ? -1 : x);   // x first of a next pair?
-                if (np >= 0 && x + 1 < JW && jj >= 0 && jj < 16) {
-                    f32x4* row = reinterpret_cast<f32x4*>(Bn + (wave * 16 + jj) * 16);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) row[j] = f32x4{gv[4 * j], gv[4 * j + 1], gv[4 * j + 2], gv[4 * j + 3]};
-                }
-                if (!par) {
-                    Halo[(wave * 4 + 0) * JW + x] = gv[0];
-                    Halo[(wave * 4 + 1) * JW + x] = gv[15];
-                    Halo[(wave * 4 + 2) * JW + x] = tv[0];
-                    Halo[(wave * 4 + 3) * JW + x] = tv[15];
-                }
-            }
-            __syncthreads();
-                };
-        for (int isw = 0; isw < kInnerSweeps; ++isw)
-            for (int t = 0; t < JW; t += 2) {
-                round(std::integral_constant<int, 0>());
-                round(std::integral_constant<int, 1>());
-            }
-        // ---- Theta to LDS in fp32 for the matrix cores; a sweep reverses the
-        //      slot order, so after an odd number of sweeps output column j is
-        //      slot 63 - j (a pair whose rotations are all small keeps its
-        //      columns in place)
-        float (*Tf0)[PD] = reinterpret_cast<float (*)[PD]>(&G[0][0]);
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            Tf0[x][(kInnerSweeps & 1) ? JW - 1 - (c0 + j) : c0 + j] = static_cast<float>(tv[j]);
-        __syncthreads();
+        inner_sweep<false>(smem, wave, lane);
+    } else {
+        // ---- 3. one sweep of two-sided Jacobi on the 64 x 64 Gram
+        inner_sweep<true>(smem, wave, lane);
     }
     // ---- 4. Y_P <- Y_P Theta on the bf16 matrix cores: Theta split into
     //         three planes once (the wave's B fragments stay in registers),
@@ -820,17 +935,14 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
             }
         __syncthreads();                       // the Y_P planes overwrite Theta
         float* Y = Xtb + static_cast<int64_t>(b) * strideX;
-        if (nch > 0) {
-            pair_fetch(Y, k, col, tid, ch0 * PC, pre0, pre1);
-            pair_stash(lds, 0, tid, pre0, pre1);
-        }
+        fetch(Y, 0);
+        if (nch > 0) pair_stash(lds, 0, tid, pre);
         __syncthreads();
         const int cst[2] = {col[32 * tn + (lane & 15)], col[32 * tn + 16 + (lane & 15)]};
-        const bool vec4 = (k & 3) == 0;
         for (int it = 0; it < nit; ++it) {
             const int s = it & 1;
             const int r0 = (ch0 + it) * PC;
-            if (it + 1 < nch) pair_fetch(Y, k, col, tid, r0 + PC, pre0, pre1);
+            fetch(Y, it + 1);
             if (NG == 1 || it < nch) {
                 f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
@@ -863,7 +975,7 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
                     }
                 }
             }
-            if (it + 1 < nch) pair_stash(lds, s ^ 1, tid, pre0, pre1);
+            if (it + 1 < nch) pair_stash(lds, s ^ 1, tid, pre);
             __syncthreads();
         }
     }

@@ -1007,3 +1007,27 @@ def test_rsvd_smallest_shapes(gl, orc, m, n, r, p, q, dtype):
     else:
         Pr, _, _ = orc.rsvd_update(G.exact, r, p, q, 3)
         assert proj_dist(P, Pr) <= 1e-3
+
+
+@pytest.mark.parametrize("k", [31, 64, 65, 96, 130, 163])
+def test_rsvd_pair_launch_forms_agree(gl, orc, k):
+    """The small SVD's steps run with four groups of waves a workgroup up to 256
+    workgroups a launch and one group above: the same bits, at sketch widths at
+    and beside the block (32), the row chunk (32) and the 16-byte row (k % 4),
+    with fewer chunks than groups and more. Spectrum and noise leave both large
+    and small rotations (the one-sweep and the all-at-once form). Against the
+    oracle with the usual bounds (P from a gapped spectrum: 1e-3)."""
+    import torch
+    m, n, r = max(k, 40), 2 * k + 3, max(k // 2, 1)
+    spec = gi.spectrum_geometric(m, 0.9 if k < 100 else 0.96)
+    spec[r:] *= 0.1
+    G = gi.store(gi.planted_gradient(m, n, spec, 1e-6, seed=k), "f32")
+    _check_rsvd(gl, orc, G, r, k - r, 1, seed=21, idx=0)
+    pairs = max(1, ((k + 31) // 32 + 1) // 2)
+    batch = 256 // pairs + 2
+    Gb = dev_stored(G).expand(batch, m, n).contiguous()
+    Pw, sw, iw = gl.galore_rsvd_update(Gb[:1].contiguous(), r, k - r, 1, 21, 0)
+    # every matrix draws its own sketch: matrix 0 is the single call's
+    Pn, sn, inn = gl.galore_rsvd_update(Gb, r, k - r, 1, 21, 0)
+    assert (inn.cpu().numpy() == 0).all() and int(iw.cpu()[0]) == 0
+    assert torch.equal(Pw[0], Pn[0]) and torch.equal(sw[0], sn[0])
