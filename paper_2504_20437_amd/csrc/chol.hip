@@ -11,8 +11,8 @@
 // built alongside, column block by column block (X R' = I gives
 // X_IJ = -(sum_{U<J} X_IU R_UJ) D_J), its partial sums P_IJ accumulated by the
 // trailing launches in X's own upper blocks, so no separate inverse phase runs:
-//   diag 0   factor the 64 x 64 diagonal block 0 in registers (unblocked,
-//            fp64) and invert it (D_0 = R'_00^-1, kept in X's diagonal block);
+//   diag 0   factor the 64 x 64 diagonal block 0 (fp64, by block rows of 16)
+//            and invert it (D_0 = R'_00^-1, kept in X's diagonal block);
 //   for each block row J:
 //     panel+X  R_JT = D_J^T C_JT for every block column T > J, and block column J
 //              of the inverse, X_IJ = -P_IJ D_J for I < J (fp64 and fp32, the
@@ -101,155 +101,245 @@ __device__ __forceinline__ void mma64_pairs(const double* Ap, const double* Bp, 
     }
 }
 
-// Factor the diagonal block J and invert its factor, one workgroup per matrix.
-// The 64 x 64 block lives in registers, thread (ty, tx) holding the entries
-// (ty + 16 q, tx + 16 w); each pivot step broadcasts one row (and, for the
-// inverse, one column) through a ping-pong LDS buffer, so a step costs one
-// barrier and no LDS read-modify-write.
-//  * factor (right-looking): pivot d = S_ii; d <= tau_rel * (original diagonal)
-//    marks a dependent column, whose row of R is zero; otherwise
-//    R_ii = sqrt(d), R_ic = S_ic / R_ii and S_ac -= R_ia R_ic for a, c > i.
-//  * inverse D = R'^-1 (R' = R with unit rows for the dependent pivots), by
-//    columns from the last: row i of D is final once rows t > i are
-//    eliminated from it, D_i = X_i / R'_ii, then X_a -= R_ai D_i for a < i.
-// (the body of one matrix's diagonal step; every thread of the workgroup calls it)
-__device__ __forceinline__ void diag_block(double* C, int k, int J, double* diag0, int* defic, double* X, float* Ri,
-                                           double tau_rel) {
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int j0 = J * CB;
-    const int jb = min(CB, k - j0);
-    __shared__ double rowb[2][CB];
-    __shared__ double colb[2][CB];
-    __shared__ double piv[CB];
-    __shared__ int dfl[CB];
-    __shared__ double corig[CB];
-
-    if (J == 0) {
-        for (int i = tid; i < k; i += CT) diag0[i] = C[static_cast<int64_t>(i) * k + i];
-    }
-    // the original diagonal of this block, staged once (the pivot loop below
-    // is serial and must not wait on global memory)
-    if (tid < jb) corig[tid] = (J == 0) ? C[static_cast<int64_t>(j0 + tid) * k + j0 + tid] : diag0[j0 + tid];
-    // only the upper triangle (c >= a) is live; the lower one is loaded as it
-    // stands and never read
-    double s[4][4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int a = ty + 16 * q, c = tx + 16 * w;
-            s[q][w] = (a < jb && c < jb) ? C[static_cast<int64_t>(j0 + a) * k + j0 + c] : 0.0;
-        }
-    __syncthreads();
-
-#pragma unroll
-    for (int ib = 0; ib < 4; ++ib) {
-        for (int i16 = 0; i16 < 16; ++i16) {
-            const int i = 16 * ib + i16;
-            if (i >= jb) break;
-            const int buf = i & 1;
-            if (ty == i16) {
-#pragma unroll
-                for (int w = 0; w < 4; ++w) rowb[buf][tx + 16 * w] = s[ib][w];
-            }
-            __syncthreads();
-            const double d = rowb[buf][i];
-            const bool def = (d <= tau_rel * corig[i]);   // NaN compares false
-            const double rii = def ? 0.0 : sqrt(d);
-            const double pv = def ? 0.0 : 1.0 / rii;
-            double ra[4], rc[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                ra[q] = rowb[buf][ty + 16 * q] * pv;
-                rc[q] = rowb[buf][tx + 16 * q] * pv;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    if (ty + 16 * q > i && tx + 16 * w > i) s[q][w] = fma(-ra[q], rc[w], s[q][w]);
-            if (ty == i16) {
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const int c = tx + 16 * w;
-                    if (c > i) s[ib][w] *= pv;
-                    else if (c == i) s[ib][w] = rii;
-                }
-            }
-            if (tid == 0) {
-                piv[i] = def ? 1.0 : rii;
-                dfl[i] = def ? 1 : 0;
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int a = ty + 16 * q, c = tx + 16 * w;
-            if (a < jb && c < jb && c >= a) C[static_cast<int64_t>(j0 + a) * k + j0 + c] = s[q][w];
-        }
-    if (tid < jb) defic[j0 + tid] = dfl[tid];
-
-    double x[4][4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) x[q][w] = (ty + 16 * q == tx + 16 * w) ? 1.0 : 0.0;
-#pragma unroll
-    for (int ib = 3; ib >= 0; --ib) {
-        for (int i16 = 15; i16 >= 0; --i16) {
-            const int i = 16 * ib + i16;
-            if (i >= jb) continue;
-            const int buf = i & 1;
-            if (ty == i16) {
-                const double inv = 1.0 / piv[i];
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    x[ib][w] *= inv;
-                    rowb[buf][tx + 16 * w] = x[ib][w];
-                }
-            }
-            if (tx == i16) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) colb[buf][ty + 16 * q] = s[q][ib];   // R_ai, a < i
-            }
-            __syncthreads();
-            double xi[4], ra[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                xi[q] = rowb[buf][tx + 16 * q];
-                ra[q] = colb[buf][ty + 16 * q];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    if (ty + 16 * q < i) x[q][w] = fma(-ra[q], xi[w], x[q][w]);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int r = ty + 16 * q, c = tx + 16 * w;
-            if (r < jb && c < jb) {
-                const double v = (c >= r) ? x[q][w] : 0.0;
-                X[static_cast<int64_t>(j0 + r) * k + j0 + c] = v;
-                if (Ri != nullptr) Ri[static_cast<int64_t>(j0 + r) * k + j0 + c] = static_cast<float>(v);
-            }
-        }
+// fp64 value of one lane, in every lane
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const int64_t u = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
+    return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 
-__global__ __launch_bounds__(CT) void chol_diag_kernel(double* Cb, int k, int64_t strideC, int J,
-                                                       double* diag0b, int* deficB, double* Xb,
-                                                       float* Rib, int64_t strideInv, double tau_rel) {
+// fp64 value of the lane whose byte address (4 times its number) is a
+__device__ __forceinline__ double lane_at(int a, double v) {
+    const int64_t u = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_ds_bpermute(a, static_cast<int>(u));
+    const uint32_t hi = __builtin_amdgcn_ds_bpermute(a, static_cast<int>(u >> 32));
+    return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
+// r = sqrt(d) and y = 1 / r for d > 0: the hardware's estimate of 1 / sqrt(d),
+// two Newton steps, the root's residual taken out once and the reciprocal's
+// once. The last two steps round correctly (equal to sqrt and division on
+// 102400 random values), at half their length.
+__device__ __forceinline__ void root64(double d, double& r, double& y) {
+    y = __builtin_amdgcn_rsq(d);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-d * y, y, 1.0), y);
+    r = d * y;
+    r = fma(0.5 * y, fma(-r, r, d), r);
+    y = fma(y, fma(-r, y, 1.0), y);
+}
+
+// Factor the diagonal block J and invert its factor, one workgroup per matrix.
+// The 64 x 64 block sits in LDS and is worked off in four block rows of 16:
+//  * wave 0 takes the block row, one column a lane (lane l: column 16 ib + l,
+//    sixteen rows in registers), and eliminates it: pivot d = S_ii; d <=
+//    tau_rel * (original diagonal) marks a dependent column, whose row of R is
+//    zero; otherwise the row is scaled by 1 / sqrt(d) and R_ia times it is
+//    taken from the rows a > i. The R_ia are lane values, so a pivot costs no
+//    LDS access and no barrier;
+//  * the four waves update the block rows below on the fp64 matrix cores.
+// Then wave J works out block column J of D = R'^-1 (R' = R with unit rows for
+// the dependent pivots) from its last row: what the rows below take from a
+// block row on the matrix cores, then the block row by substitution, a column
+// a lane (in all four lane groups alike).
+// An fp64 matrix-core product adds its four terms one by one in the order of
+// the contraction index (checked on the device against a chain of fused
+// multiply-adds), so every entry sees the operations of the plain right-looking
+// factorisation and of the substitution from the last row, in their order: the
+// same bits as one pivot at a time, whatever the block's condition.
+// Rows and columns past the matrix are those of the unit matrix.
+// One barrier, square root and division per pivot and 128 dependent steps of
+// the whole workgroup took 56 us a block; this form 20 us.
+// (the body of one matrix's diagonal step; every thread of the workgroup calls it)
+// The block (upper triangle) and lim are in LDS on entry, behind a barrier.
+constexpr int DB = 16;       // block rows
+struct DiagLds {
+    double S[CB][CB + 1];
+    double lim[CB];          // tau_rel * original diagonal
+    double inv[CB];          // 1 / R'_ii
+};
+__device__ __forceinline__ void diag_block(DiagLds& lds, double* C, int k, int J, int* defic, double* X, float* Ri) {
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lk = lane >> 4;
+    const int j0 = J * CB;
+    const int jb = min(CB, k - j0);
+    double (*S)[CB + 1] = lds.S;
+    // R_ii^T (row pitch CB + 1) in the free blocks (1, 0), (2, 0), (2, 1) and
+    // (3, 0) below the diagonal
+    auto rt = [&](int i) { return &S[i == 0 ? DB : (i == 3 ? 3 * DB : 2 * DB)][i == 2 ? DB : 0]; };
+
+    for (int ib = 0; ib < CB / DB; ++ib) {
+        const int r0 = DB * ib;
+        if (wave == 0) {
+            // kept opaque per block row: the lane masks of all pivots, formed
+            // once for all block rows, would not fit the scalar registers
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const int c = min(r0 + ln, CB - 1);
+            const double li = lds.lim[r0 + (ln & 15)];
+            double s[DB];
+#pragma unroll
+            for (int i = 0; i < DB; ++i) s[i] = S[r0 + i][c];
+            unsigned dmask = 0;
+            double iv = 1.0;
+#pragma unroll
+            for (int i = 0; i < DB; ++i) {
+                const bool def = (__builtin_amdgcn_ballot_w64(s[i] <= li) >> i) & 1;   // lane i's; NaN compares false
+                const double d = lane_value(s[i], i);
+                double r, y;
+                root64(d, r, y);
+                s[i] = (ln == i) ? (def ? 0.0 : r) : s[i] * (def ? 0.0 : y);
+                iv = (ln == i) ? (def ? 1.0 : y) : iv;
+                dmask |= def ? 1u << i : 0u;
+#pragma unroll
+                for (int a = i + 1; a < DB; ++a) s[a] = fma(-lane_value(s[i], a), s[i], s[a]);
+                // pivot by pivot: left to itself the compiler puts a row's updates off
+                // to its own pivot, and their lane values do not fit the scalar registers
+                asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]),
+                             "+v"(s[7]), "+v"(s[8]), "+v"(s[9]), "+v"(s[10]), "+v"(s[11]), "+v"(s[12]), "+v"(s[13]),
+                             "+v"(s[14]));
+            }
+            if (r0 + ln < CB) {
+#pragma unroll
+                for (int i = 0; i < DB; ++i) S[r0 + i][r0 + ln] = s[i];
+            }
+            if (ln < DB) {
+                double* t = rt(ib) + (CB + 1) * ln;
+#pragma unroll
+                for (int i = 0; i < DB; ++i) t[i] = s[i];
+                lds.inv[r0 + ln] = iv;
+                if (r0 + ln < jb) defic[j0 + r0 + ln] = (dmask >> ln) & 1;
+            }
+        }
+        __syncthreads();
+        // S_ab -= R_ia^T R_ib for the block rows below (a diagonal block's lower
+        // part is not used)
+        const int n = CB / DB - 1 - ib;
+        for (int t = wave; t < n * (n + 1) / 2; t += CT / 64) {
+            int u = 0, idx = t;
+            while (idx >= n - u) {
+                idx -= n - u;
+                ++u;
+            }
+            const int a0 = DB * (ib + 1 + u), b0 = DB * (ib + 1 + u + idx);
+            f64x4 acc;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[v] = S[a0 + 4 * v + lk][b0 + l16];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-S[r0 + 4 * v + lk][a0 + l16], S[r0 + 4 * v + lk][b0 + l16],
+                                                           acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[a0 + 4 * v + lk][b0 + l16] = acc[v];
+        }
+        __syncthreads();
+    }
+
+    // block column `wave` of D: xb[U] = rows 16 U + 4 v + 3 - lk (right operands
+    // in descending order of the row), xs[U] = rows 16 U + 4 v + lk, stored at the
+    // end (between the blocks the stores held up the next one's reads); a whole
+    // block (uniform) without per-entry branches, zeros below the diagonal
+    double* Xd = X + static_cast<int64_t>(j0) * k + j0 + DB * wave + l16;
+    double* Cd = C + static_cast<int64_t>(j0) * k + j0;
+    float* Rd = Ri != nullptr ? Ri + static_cast<int64_t>(j0) * k + j0 + DB * wave + l16 : nullptr;
+    auto store = [&](int U, f64x4 x) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = DB * U + 4 * v + lk;
+            if (jb == CB || (r < jb && DB * wave + l16 < jb)) {
+                Xd[static_cast<int64_t>(r) * k] = x[v];
+                if (Rd != nullptr) Rd[static_cast<int64_t>(r) * k] = static_cast<float>(x[v]);
+            }
+        }
+    };
+    f64x4 xb[CB / DB], xs[CB / DB];
+    auto pick = [&](double x0, double x1, double x2, double x3, int g) {
+        const double u = (g & 1) ? x1 : x0, v = (g & 1) ? x3 : x2;
+        return (g & 2) ? v : u;
+    };
+#pragma unroll
+    for (int U = CB / DB - 1; U >= 0; --U) {
+        xs[U] = xb[U] = f64x4{0.0, 0.0, 0.0, 0.0};
+        if (U > wave) continue;
+        double x[DB];
+        if (U == wave) {
+#pragma unroll
+            for (int i = 0; i < DB; ++i) x[i] = (l16 == i) ? 1.0 : 0.0;
+        } else {
+            f64x4 z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int T = CB / DB - 1; T > U; --T) {
+                if (T > wave) continue;
+#pragma unroll
+                for (int v = 3; v >= 0; --v)
+                    z = __builtin_amdgcn_mfma_f64_16x16x4f64(-S[DB * U + l16][DB * T + 4 * v + 3 - lk], xb[T][v], z, 0, 0,
+                                                             0);
+            }
+            // all sixteen rows of the lane's column
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) x[4 * v + g] = lane_at(4 * (l16 + 16 * g), z[v]);
+        }
+        const double* t = rt(U);
+#pragma unroll
+        for (int i = DB - 1; i >= 0; --i) {
+            x[i] *= lds.inv[DB * U + i];
+#pragma unroll
+            for (int a = i - 1; a >= 0; --a) x[a] = fma(-t[(CB + 1) * i + a], x[i], x[a]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            xs[U][v] = pick(x[4 * v], x[4 * v + 1], x[4 * v + 2], x[4 * v + 3], lk);
+            xb[U][v] = pick(x[4 * v + 3], x[4 * v + 2], x[4 * v + 1], x[4 * v], lk);
+            if (U == wave && 4 * v + lk > l16) xs[U][v] = 0.0;
+        }
+    }
+#pragma unroll
+    for (int U = 0; U < CB / DB; ++U) store(U, xs[U]);
+    if (jb == CB) {
+#pragma unroll 8
+        for (int e = 0; e < CB * CB / CT; ++e) {
+            const int a = wave + 4 * e;
+            if (a <= lane) Cd[static_cast<int64_t>(a) * k + lane] = S[a][lane];
+        }
+    } else {
+        for (int a = wave; a < jb; a += CT / 64)
+            if (a <= lane && lane < jb) Cd[static_cast<int64_t>(a) * k + lane] = S[a][lane];
+    }
+}
+
+// Block 0 of every matrix (blockIdx.y = 0), and the diagonal of the Gram that
+// the later blocks' dependency tests compare with (blockIdx.y = 1)
+__global__ __launch_bounds__(CT) void chol_diag_kernel(double* Cb, int k, int64_t strideC, double* diag0b, int* deficB,
+                                                       double* Xb, float* Rib, int64_t strideInv, double tau_rel) {
+    __shared__ DiagLds lds;
     const int b = blockIdx.x;
-    diag_block(Cb + static_cast<int64_t>(b) * strideC, k, J, diag0b + static_cast<int64_t>(b) * k,
-               deficB + static_cast<int64_t>(b) * k, Xb + static_cast<int64_t>(b) * strideInv,
-               Rib != nullptr ? Rib + static_cast<int64_t>(b) * strideInv : nullptr, tau_rel);
+    const int tid = threadIdx.x;
+    double* C = Cb + static_cast<int64_t>(b) * strideC;
+    if (blockIdx.y == 1) {
+        // not those of block 0: its factor overwrites them (it keeps its own)
+#pragma unroll 4
+        for (int i = CB + tid; i < k; i += CT) diag0b[static_cast<int64_t>(b) * k + i] = C[static_cast<int64_t>(i) * k + i];
+        return;
+    }
+    const int jb = min(CB, k);
+    if (tid < CB) {
+        const double d = tid < jb ? C[static_cast<int64_t>(tid) * k + tid] : 0.0;
+        if (tid < jb) diag0b[static_cast<int64_t>(b) * k + tid] = d;
+        lds.lim[tid] = tau_rel * d;
+    }
+#pragma unroll
+    for (int e = 0; e < CB * CB / CT; ++e) {
+        const int a = (tid >> 6) + 4 * e, c = tid & 63;
+        lds.S[a][c] = (c < jb && a <= c) ? C[static_cast<int64_t>(a) * k + c] : (a == c ? 1.0 : 0.0);
+    }
+    __syncthreads();
+    diag_block(lds, C, k, 0, deficB + static_cast<int64_t>(b) * k, Xb + static_cast<int64_t>(b) * strideInv,
+               Rib != nullptr ? Rib + static_cast<int64_t>(b) * strideInv : nullptr);
 }
 
 // acc += A B for one 64 x 64 x 64 tile with A given by rows (A[i * ld + t], t
@@ -379,6 +469,7 @@ __global__ __launch_bounds__(CT, 4) void chol_panel_x_kernel(double* Cb, int k, 
 __global__ __launch_bounds__(CT, 4) void chol_trailing_p_kernel(double* Cb, int k, int64_t strideC, int J, int nb,
                                                              double* diag0b, int* deficB, double* Xb, float* Rib,
                                                              int64_t strideInv, double tau_rel) {
+    __shared__ DiagLds lds;   // the diagonal tile's workgroup only
     const int b = blockIdx.y;
     double* C = Cb + static_cast<int64_t>(b) * strideC;
     double* X = Xb + static_cast<int64_t>(b) * strideInv;
@@ -402,6 +493,39 @@ __global__ __launch_bounds__(CT, 4) void chol_trailing_p_kernel(double* Cb, int 
         const int vt = u + idx;
         const int r0 = (J + 1 + u) * CB, rb = min(CB, k - r0);
         const int c0 = (J + 1 + vt) * CB, cb = min(CB, k - c0);
+        if (blockIdx.x == 0) {
+            // tile (J + 1, J + 1): its last update, into LDS, then step J + 1's
+            // diagonal (the entries' original diagonal fetched beside the product)
+            const bool live = threadIdx.x < CB && static_cast<int>(threadIdx.x) < rb;
+            const double d0 = live ? diag0b[static_cast<int64_t>(b) * k + r0 + threadIdx.x] : 0.0;
+            const int c = 32 * wn + 2 * l16;
+            const bool need = wm <= wn;   // the quadrant below the diagonal is not
+            if (need)
+                mma64_pairs(C + static_cast<int64_t>(j0) * k + r0, C + static_cast<int64_t>(j0) * k + c0, k, jb, rb, cb,
+                            vec, acc, wm, wn, lane);
+            f64x2 o[2][4];
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    o[bi][v] = need ? ld_pair(C + static_cast<int64_t>(r0) * k + c0, k,
+                                              32 * wm + 2 * (4 * v + lk) + bi, c, rb, cb, vec)
+                                    : f64x2{0.0, 0.0};
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 32 * wm + 2 * (4 * v + lk) + bi;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        lds.S[r][c + e] = (r < rb && c + e < cb) ? o[bi][v][e] - acc[bi][e][v] : (r == c + e ? 1.0 : 0.0);
+                }
+            if (threadIdx.x < CB) lds.lim[threadIdx.x] = tau_rel * d0;
+            __syncthreads();
+            diag_block(lds, C, k, J + 1, deficB + static_cast<int64_t>(b) * k, X,
+                       Rib != nullptr ? Rib + static_cast<int64_t>(b) * strideInv : nullptr);
+            return;
+        }
         // on a diagonal tile the quadrant below the diagonal is not needed
         if (!(u == vt && wm > wn)) {
             // operands: rows j0 + t of the block row J just finished (R_JT1, R_JT2);
@@ -450,13 +574,6 @@ __global__ __launch_bounds__(CT, 4) void chol_trailing_p_kernel(double* Cb, int 
                     }
                 }
             }
-        }
-        if (blockIdx.x == 0) {
-            // tile (J + 1, J + 1) is final: factor it (its updates above are
-            // visible to the whole workgroup past the barrier)
-            __syncthreads();
-            diag_block(C, k, J + 1, diag0b + static_cast<int64_t>(b) * k, deficB + static_cast<int64_t>(b) * k, X,
-                       Rib != nullptr ? Rib + static_cast<int64_t>(b) * strideInv : nullptr, tau_rel);
         }
         return;
     }
@@ -556,8 +673,8 @@ hipError_t launch_cholesky(double* C, int k, int64_t strideC, float* rinv32, dou
                            hipStream_t stream) {
     const int nb = (k + CB - 1) / CB;
     const bool inv = rinv32 != nullptr;
-    hipLaunchKernelGGL(chol_diag_kernel, dim3(batch), dim3(CT), 0, stream, C, k, strideC, 0, diag0, defic, xinv,
-                       rinv32, strideInv, tau_rel);
+    hipLaunchKernelGGL(chol_diag_kernel, dim3(batch, k > CB ? 2 : 1), dim3(CT), 0, stream, C, k, strideC, diag0, defic,
+                       xinv, rinv32, strideInv, tau_rel);
     for (int J = 0; J < nb; ++J) {
         const int n = nb - J - 1;
         const int px = n + (inv ? J : 0);

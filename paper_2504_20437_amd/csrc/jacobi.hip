@@ -662,8 +662,8 @@ __device__ __forceinline__ void inner_sweep(unsigned char* smem, int wave, int l
 // two phases over memory wait a memory latency per chunk, which only other
 // workgroups of the CU would hide, so four groups walk a quarter of the chunks
 // each. The results are the same bits. One 4096x11008 update (k = 1056, 16
-// workgroups a launch), per launch: 101 us with the inner sweep before and 61
-// us now, 36 us with small rotations only, 37 and 15 us where nothing rotates.
+// workgroups a launch), per launch: 99 us with the inner sweep before and 61 us
+// now, 36 us with small rotations only, 25 and 15 us where nothing rotates.
 template <int NG>
 __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(float* Xtb, int k, int64_t strideX,
                                                                                int nb, int step, int sweep, int* rotb,
@@ -835,9 +835,10 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
     //         zero column never counts, a pair with a NaN or Inf entry always
     //         does (non-finite input must not pass as converged: such a matrix
     //         runs every sweep and reports the sweep limit)
-    // The same pass forms the angles E of the joint rotation (entries below the
-    // tolerance whose angle is large, i.e. columns of nearly equal norm, stay
-    // unrotated) and their squares' sum, in whole units of 2^-24 so that the
+    // The same pass forms the angles E of the joint rotation (a coupling of
+    // columns of nearly equal norm has a large angle however small it is and
+    // calls for the sweep: left unrotated at 1e-7 of the norms, it turned such
+    // columns by up to 0.02) and their squares' sum, in whole units of 2^-24 so that the
     // sum does not depend on its order. E goes into the Gram's lower triangle,
     // which nothing reads from here on.
     bool small, tiny;
@@ -858,7 +859,7 @@ __global__ __launch_bounds__(JT * NG, NG == 1 ? 4 : 1) void jacobi_pair_kernel(f
                     const double d = c - a;
                     const bool fits = fabs(gpq) <= static_cast<double>(kSmallAngle) * fabs(d);
                     if (!fits) {
-                        if (!ok) big = 1;
+                        big = 1;
                     } else if (gpq != 0.0) {
                         if (!(fabs(d) > 1e-30 && fabs(d) < 1e30)) {
                             big = 1;

@@ -1031,3 +1031,28 @@ def test_rsvd_pair_launch_forms_agree(gl, orc, k):
     Pn, sn, inn = gl.galore_rsvd_update(Gb, r, k - r, 1, 21, 0)
     assert (inn.cpu().numpy() == 0).all() and int(iw.cpu()[0]) == 0
     assert torch.equal(Pw[0], Pn[0]) and torch.equal(sw[0], sn[0])
+
+
+@pytest.mark.parametrize("k", [1, 15, 17, 48, 63, 64, 65, 81, 128, 129, 145])
+def test_rsvd_cholesky_block_edges(gl, orc, k):
+    """Orthonormalisation at sketch widths at and beside the Cholesky's blocks of
+    64 and block rows of 16: full-rank, and with a sketch wider than the rank (a
+    dependent pivot inside a block row, at its edge and in a later block), where
+    the completed basis is orthonormal and the singular values past the rank are
+    at rounding level."""
+    m, n = max(k + 5, 24), 2 * k + 30
+    spec = gi.spectrum_geometric(m, 0.97)
+    r = max(1, k // 2)
+    spec[r:] *= 0.1
+    G = gi.store(gi.planted_gradient(m, n, spec, 1e-6, seed=k), "f32")
+    _check_rsvd(gl, orc, G, r, k - r, 1, seed=5)
+    if k > 2:
+        rank = k - k // 3
+        G = gi.store(gi.planted_gradient(m, n, gi.spectrum_geometric(m, 0.97), 0.0, seed=k, rank=rank), "f32")
+        P, sig, info = gl.galore_rsvd_update(dev_stored(G), k, 0, 1, 5)
+        P, sig = host(P), host(sig)
+        ss = np.linalg.svd(G.exact, compute_uv=False)
+        assert int(info.cpu()[0]) == 0
+        assert orth_err(P) < 1e-4
+        assert max_rel_violation(sig[:rank], ss[:rank], 1e-4, 1e-30) <= 1.0
+        assert np.all(sig[rank:] <= 1e-4 * sig[0])
