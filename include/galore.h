@@ -85,7 +85,7 @@ GALORE_API int galore_sketch(float* omega, int64_t l, int64_t k, uint64_t seed, 
 /*
  * Bytes of workspace galore_rsvd_update needs for `batch` m x n matrices with
  * rank r, oversampling p and gradient storage g_dtype (a bf16 gradient also
- * holds its transposed copy and the bf16 split of the fp32 sketch operands).
+ * holds a padded copy of it and the bf16 split of the fp32 sketch operands).
  * Returns 0 for invalid sizes or dtype.
  */
 GALORE_API size_t galore_rsvd_workspace_size(int64_t m, int64_t n, int32_t r, int32_t p, int32_t batch,
@@ -199,8 +199,9 @@ GALORE_API int galore_rsvd_update_traced(const void* G, int32_t g_dtype, int64_t
 /*
  * Bytes of workspace galore_project uses for `batch` m x n matrices with rank
  * r and gradient storage g_dtype: for a bf16 gradient, the three bf16 planes
- * of P^T that feed the bf16 matrix cores; 0 for an fp32 gradient (which needs
- * none) and for invalid sizes or dtype.
+ * of P^T that feed the bf16 matrix cores and, where s is no multiple of 32 or n
+ * none of 8, a copy of the gradient with both sides padded to multiples of 32;
+ * 0 for an fp32 gradient (which needs none) and for invalid sizes or dtype.
  */
 GALORE_API size_t galore_project_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch, int32_t g_dtype);
 
@@ -211,13 +212,16 @@ GALORE_API size_t galore_project_workspace_size(int64_t m, int64_t n, int32_t r,
  * Workspace (optional, device, 256-byte aligned, scratch): with a bf16
  * gradient and at least galore_project_workspace_size(...) bytes, P is split
  * there into three bf16 planes (P = P1 + P2 + P3 exactly to fp32 rounding)
- * and the product runs on the bf16 matrix cores with fp32 accumulation
- * (16-byte aligned rows of G and s a multiple of 32; otherwise, and with
- * workspace NULL, it runs on the fp32 matrix cores). The result is the
+ * and the product runs on the bf16 matrix cores with fp32 accumulation, on G
+ * itself (16-byte aligned rows and s a multiple of 32) or, for the sizes that
+ * galore_project_workspace_size names, on its padded copy. Otherwise, and with
+ * workspace NULL, it runs on the fp32 matrix cores. The result is the
  * fp32-accurate product either way.
  * Errors: NULL P/G/R -> INVALID_ARG; sizes/ld invalid, r > s -> SHAPE;
- * misaligned workspace, or bf16 G with a non-NULL workspace shorter than
- * galore_project_workspace_size(...) -> WORKSPACE.
+ * misaligned workspace, or bf16 G with a non-NULL workspace shorter than the
+ * planes (6 bytes for each of r x s rounded up to 8, rounded up per plane to
+ * 128 bytes and in all to 256) -> WORKSPACE. A workspace of the planes alone,
+ * without the copy, is taken and leaves such sizes to the fp32 matrix cores.
  */
 GALORE_API int galore_project(const float* P, int64_t ldp, int64_t stride_p, const void* G, int32_t g_dtype,
                    int64_t m, int64_t n, int64_t ldg, int64_t stride_g, int32_t r, float* R,
@@ -228,7 +232,7 @@ GALORE_API int galore_project(const float* P, int64_t ldp, int64_t stride_p, con
  * galore_project without a workspace, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving or training loops,
  * harnesses that forbid allocation): the same projection, kernels and results
- * as galore_project with a workspace of galore_project_workspace_size(...)
+ * as galore_project with a workspace of galore_project_noalloc_max_bytes()
  * bytes, with that scratch held instead in a fixed-size device array inside
  * the library (galore_project_noalloc_max_bytes() bytes, 64 MiB; one copy on
  * each device the library runs on, kept until the process ends). The caller
@@ -239,9 +243,8 @@ GALORE_API int galore_project(const float* P, int64_t ldp, int64_t stride_p, con
  * device (concurrent streams or host threads) race and must be serialised by
  * the caller. The array needs no initial contents (each call writes every byte
  * it reads).
- * Errors: as galore_project; a bf16 gradient whose workspace size
- * (galore_project_workspace_size) exceeds galore_project_noalloc_max_bytes()
- * -> WORKSPACE, checked before any device call; the lookup of the array failing
+ * Errors: as galore_project; a bf16 gradient whose planes of P^T exceed
+ * galore_project_noalloc_max_bytes() -> WORKSPACE, checked before any device call; the lookup of the array failing
  * -> HIP. An fp32 gradient needs no scratch (fp32 matrix cores).
  */
 GALORE_API size_t galore_project_noalloc_max_bytes(void);
@@ -387,8 +390,8 @@ GALORE_API size_t galore_project_quantized_workspace_size(int64_t m, int64_t n, 
 /*
  * Projection with the low-bit projector: R = Pq^T A with Pq = code * scale
  * (galore_quantize_projector's codes and scales; paper §3 projection). With a
- * bf16 gradient (16-byte aligned rows, s a multiple of 32 for m <= n) the
- * codes form one exact bf16 plane, the product runs once on the bf16 matrix
+ * bf16 gradient (16-byte aligned rows and s a multiple of 32, or the padded copy
+ * that galore_project describes) the codes form one exact bf16 plane, the product runs once on the bf16 matrix
  * cores with fp32 accumulation and each row of R is multiplied by its scale;
  * otherwise Pq is rounded to fp32 and the product runs on the fp32 matrix
  * cores. Shapes and errors as galore_project, plus those of the codes;

@@ -10,18 +10,13 @@
 // products accumulated in fp32: the same arithmetic class as an fp32 GEMM, on
 // a unit with 16x the fp32 matrix rate.
 //
-// Operand layouts (both with the reduction index contiguous, so that a lane's
-// eight consecutive k values are one 16-byte LDS read):
-//   A: bf16, M x K rows (G itself, or its transposed copy made by
-//      transpose_bf16 for the products with A^T);
+// Operand layouts:
+//   A: bf16, M x K rows (K-contiguous) or K x M rows (M-contiguous): G itself
+//      in both orientations, or its padded copy (pad_bf16);
 //   B: three bf16 planes, each N x K rows (made by split3_transpose from the
 //      fp32 K x N operand).
-// C = alpha * A B + beta * C in fp32, M x N row-major.
-//
-// Tile 128 x 128 x 64, four wave64s each owning 64 x 64 (2 x 2 blocks of
-// 32 x 32), LDS rows padded to 72 bf16 (144 bytes: the 16 lanes of a 16-byte
-// read fall on distinct banks), next tile prefetched in registers, XCD-aware
-// row-grouped tile order.
+// C = alpha * A B + beta * C in fp32, M x N row-major or transposed.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -32,34 +27,47 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int XM = 128;
-constexpr int XN = 128;
-constexpr int XK = 64;
-constexpr int XKP = XK + 8;     // padded LDS row (bf16): 144 bytes, 16-byte lane reads conflict-free
-constexpr int XT = 256;
-
-
 // --------------------------------------------------------------------------
-// dst (cols x rows, ld ldd) = src^T (src rows x cols, ld lds), bf16, 64 x 64 tiles
+// dst (rows_pad x ldd, ldd a multiple of 8) = src (rows x cols, ld lds), bf16,
+// zeros past the matrix. Any pitch and two-byte alignment of src: a thread
+// writes eight entries with one 16-byte store and reads them as the four dwords
+// they are, or as the five that hold them, shifted by one entry (away from the
+// row's ends; singly there). 8 x 2048x5461 in 63 us, 2.8 TB/s.
 // --------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* srcb, int64_t lds, int64_t strideS,
-                                                             uint16_t* dstb, int64_t ldd, int64_t strideD, int rows,
-                                                             int cols) {
-    __shared__ uint16_t tile[64][66];
+__global__ __launch_bounds__(256) void pad_bf16_kernel(const uint16_t* srcb, int64_t lds, int64_t strideS,
+                                                       uint16_t* dstb, int64_t ldd, int64_t strideD, int rows,
+                                                       int cols) {
     const int b = blockIdx.z;
-    const uint16_t* src = srcb + static_cast<int64_t>(b) * strideS;
-    uint16_t* dst = dstb + static_cast<int64_t>(b) * strideD;
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const int r = r0 + i, c = c0 + tx;
-        tile[i][tx] = (r < rows && c < cols) ? src[static_cast<int64_t>(r) * lds + c] : 0;
+    const int r = blockIdx.y;
+    const int c = 8 * (blockIdx.x * blockDim.x + threadIdx.x);
+    if (c >= ldd) return;
+    const uint16_t* src = srcb + static_cast<int64_t>(b) * strideS + static_cast<int64_t>(r) * lds + c;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    if (r < rows && c < cols) {
+        const bool odd = (reinterpret_cast<uintptr_t>(src) & 2) != 0;
+        if (c > 0 && c + 9 <= cols) {
+            const uint32_t* q = reinterpret_cast<const uint32_t*>(src - (odd ? 1 : 0));
+            const uint32_t u0 = q[0], u1 = q[1], u2 = q[2], u3 = q[3];
+            if (odd) {
+                const uint32_t u4 = q[4];
+                w[0] = (u0 >> 16) | (u1 << 16);
+                w[1] = (u1 >> 16) | (u2 << 16);
+                w[2] = (u2 >> 16) | (u3 << 16);
+                w[3] = (u3 >> 16) | (u4 << 16);
+            } else {
+                w[0] = u0;
+                w[1] = u1;
+                w[2] = u2;
+                w[3] = u3;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (c + e < cols) w[e >> 1] |= static_cast<uint32_t>(src[e]) << (16 * (e & 1));
+        }
     }
-    __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int c = c0 + i, r = r0 + tx;
-        if (c < cols && r < rows) dst[static_cast<int64_t>(c) * ldd + r] = tile[tx][i];
-    }
+    *reinterpret_cast<uint4*>(dstb + static_cast<int64_t>(b) * strideD + static_cast<int64_t>(r) * ldd + c) =
+        make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // --------------------------------------------------------------------------
@@ -188,130 +196,13 @@ struct Bx3Args {
     int b_upper;                // direct kernel: B upper triangular (B[kk][n] = 0 for kk > n)
     unsigned* cmax;             // direct kernel, row-major C: per-column max of |C| (bits; atomicMax), or null
     int64_t strideCM;
+    int mload;                  // M-contiguous A: entries per row that may be loaded (>= M, a multiple of 8)
     const float* nscale;        // direct kernel: C(m, n) scaled by nscale[n] (per matrix at strideNS), or null
     int64_t strideNS;
 };
 
-__global__ __launch_bounds__(XT, 2) void gemm_bf16x3_kernel(Bx3Args g, int vec) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[XM][XKP];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[3][XN][XKP];
-
-    const int num_n = gridDim.x, num_m = gridDim.y;
-    const int tiles = num_n * num_m;
-    const int lin = blockIdx.x + num_n * (blockIdx.y + num_m * blockIdx.z);
-    const int logical = xcd_logical_id(lin, tiles * gridDim.z);
-    const int bz = logical / tiles;
-    int tm, tn;
-    grouped_tile(logical - bz * tiles, num_m, num_n, 8, tm, tn);
-    const uint16_t* A = g.A + static_cast<int64_t>(bz) * g.strideA;
-    const uint16_t* B = g.B + static_cast<int64_t>(bz) * g.strideB;
-    float* C = g.C + static_cast<int64_t>(bz) * g.strideC;
-    const int M = g.M, N = g.N, K = g.K;
-    const int row0 = tm * XM, col0 = tn * XN;
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // loader: a 128 x 64 bf16 tile is 1024 segments of 8 (16 bytes); thread t
-    // moves segments t + 256 e, e < 4 (row seg / 8, k offset 8 (seg % 8))
-    constexpr int SEGS = XM * XK / 8 / XT;
-    constexpr int SPR = XK / 8;     // segments per row
-    uint4 ra[SEGS], rb[3][SEGS];
-    const bool a_in = vec && row0 + XM <= M;
-    const bool b_in = vec && col0 + XN <= N;
-    auto load_rows = [&](const uint16_t* base, int64_t ld, int r0, int R, int k0, bool fast, uint4* out) {
-#pragma unroll
-        for (int e = 0; e < SEGS; ++e) {
-            const int seg = t + XT * e;
-            const int rr = r0 + seg / SPR, kk = k0 + 8 * (seg % SPR);
-            const uint16_t* src = base + static_cast<int64_t>(rr) * ld + kk;
-            if (fast && kk + 8 <= K) {
-                out[e] = *reinterpret_cast<const uint4*>(src);
-            } else {
-                uint16_t v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = (rr < R && kk + q < K) ? src[q] : 0;
-                out[e] = make_uint4(v[0] | (uint32_t(v[1]) << 16), v[2] | (uint32_t(v[3]) << 16),
-                                    v[4] | (uint32_t(v[5]) << 16), v[6] | (uint32_t(v[7]) << 16));
-            }
-        }
-    };
-    auto fetch = [&](int k0) {
-        load_rows(A, g.lda, row0, M, k0, a_in, ra);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) load_rows(B + p * g.planeStride, g.ldb, col0, N, k0, b_in, rb[p]);
-    };
-    auto stash = [&]() {
-#pragma unroll
-        for (int e = 0; e < SEGS; ++e) {
-            const int seg = t + XT * e;
-            *reinterpret_cast<uint4*>(&As[seg / SPR][8 * (seg % SPR)]) = ra[e];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(&Bs[p][seg / SPR][8 * (seg % SPR)]) = rb[p][e];
-        }
-    };
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
-
-    const int KT = (K + XK - 1) / XK;
-    const int l32 = lane & 31, lk = lane >> 5;
-    fetch(0);
-    for (int kt = 0; kt < KT; ++kt) {
-        stash();
-        __syncthreads();
-        if (kt + 1 < KT) fetch((kt + 1) * XK);
-#pragma unroll
-        for (int ks = 0; ks < XK; ks += 16) {
-            bf16x8 a[2], bq[3][2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-                a[x] = *reinterpret_cast<const bf16x8*>(&As[wm * 64 + 32 * x + l32][ks + 8 * lk]);
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    bq[p][y] = *reinterpret_cast<const bf16x8*>(&Bs[p][wn * 64 + 32 * y + l32][ks + 8 * lk]);
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int x = 0; x < 2; ++x)
-#pragma unroll
-                    for (int y = 0; y < 2; ++y)
-                        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x], bq[p][y], acc[x][y], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    // 32x32 block layout: lane holds column (lane & 31) and rows
-    // (v & 3) + 8 (v >> 2) + 4 (lane >> 5) for accumulator register v.
-    const float alpha = g.alpha, beta = g.beta;
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int c = col0 + wn * 64 + 32 * y + l32;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = row0 + wm * 64 + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
-                if (r < M && c < N) {
-                    float* dst = C + static_cast<int64_t>(r) * g.ldc + c;
-                    float val = alpha * acc[x][y][v];
-                    if (beta != 0.0f) val += beta * (*dst);
-                    *dst = val;
-                }
-            }
-        }
-    }
-}
-
 // --------------------------------------------------------------------------
-// Same product, pipelined through LDS by direct loads (K a multiple of 32,
+// The product, pipelined through LDS by direct loads (K a multiple of 32,
 // 16-byte aligned rows): tile 256 x 128 x 32, four wave64s each owning
 // 128 x 64 (4 x 2 blocks of 32 x 32, times three planes: 24 MFMAs per 16-deep
 // step against 10 fragment reads). Global memory goes straight to LDS
@@ -421,10 +312,10 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
         if constexpr (AT) {
             // M-contiguous A (A[kk * lda + i]): a stage row is one kk, 256 m
             // (32 chunks, 512 bytes), chunk c at slot c ^ (4 (kk % 4)); a direct
-            // load fills 2 rows; chunks past M load the last chunk (M % 8 == 0)
+            // load fills 2 rows; chunks past the row load its last one
             const int sr = 2 * j + (lane >> 5);
             const int slot = lane & 31;
-            const int m = min(row0 + 8 * (slot ^ (4 * (sr & 3))), M - 8);
+            const int m = min(row0 + 8 * (slot ^ (4 * (sr & 3))), g.mload - 8);
             srcA[i] = A + static_cast<int64_t>(sr) * g.lda + m;
         } else {
             const int pl = j / (YM / RPI), jb = j % (YM / RPI);   // plane, block of RPI rows
@@ -807,11 +698,17 @@ constexpr int kX6WN = GALORE_BX6_WN;       // waves across N (tile 256 x 64 WN)
 
 }  // namespace
 
-hipError_t launch_transpose_bf16(const void* src, int64_t lds, int64_t strideS, void* dst, int64_t ldd,
-                                 int64_t strideD, int rows, int cols, int batch, hipStream_t stream) {
-    dim3 grid((cols + 63) / 64, (rows + 63) / 64, batch);
-    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, stream, static_cast<const uint16_t*>(src), lds,
-                       strideS, static_cast<uint16_t*>(dst), ldd, strideD, rows, cols);
+hipError_t launch_pad_bf16(const void* src, int64_t lds, int64_t strideS, void* dst, int64_t ldd, int64_t strideD,
+                           int rows, int cols, int rows_pad, int batch, hipStream_t stream) {
+    if (ldd % 8 != 0 || strideD % 8 != 0 || reinterpret_cast<uintptr_t>(dst) % 16 != 0 || ldd < cols || rows_pad < rows)
+        return hipErrorInvalidValue;
+    // rows past 65535 of a grid axis go to the next slab
+    for (int r0 = 0; r0 < rows_pad; r0 += 65535) {
+        dim3 grid(static_cast<unsigned>((ldd / 8 + 255) / 256), std::min(65535, rows_pad - r0), batch);
+        hipLaunchKernelGGL(pad_bf16_kernel, grid, dim3(256), 0, stream,
+                           static_cast<const uint16_t*>(src) + static_cast<int64_t>(r0) * lds, lds, strideS,
+                           static_cast<uint16_t*>(dst) + static_cast<int64_t>(r0) * ldd, ldd, strideD, rows - r0, cols);
+    }
     return hipGetLastError();
 }
 
@@ -845,7 +742,7 @@ hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a
                               int64_t ldb, int64_t planeStride, int64_t strideB, float* C, int64_t ldc,
                               int64_t strideC, int c_trans, int M, int N, int K, float alpha, float beta, int batch,
                               hipStream_t stream, unsigned* cmax, int64_t strideCM, int planesB, const float* nscale,
-                              int64_t strideNS) {
+                              int64_t strideNS, int mload) {
     if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
     if (planesB != 1 && planesB != 3) return hipErrorInvalidValue;
     Bx3Args g{};
@@ -871,7 +768,11 @@ hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a
     g.strideCM = strideCM;
     g.nscale = nscale;
     g.strideNS = strideNS;
-    if (bf16x3_direct_ok(A, lda, strideA, Bplanes, ldb, planeStride, strideB, M, K, batch, a_mcontig)) {
+    g.mload = mload > 0 ? mload : M;
+    if (!bf16x3_direct_ok(A, lda, strideA, Bplanes, ldb, planeStride, strideB, g.mload, K, batch, a_mcontig) ||
+        (a_mcontig && g.mload < M))
+        return hipErrorInvalidValue;
+    {
         dim3 grid((N + YN - 1) / YN, (M + YM - 1) / YM, batch);
         if (planesB == 1) {
             if (a_mcontig)
@@ -886,15 +787,6 @@ hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a
         }
         return hipGetLastError();
     }
-    // the register-staged kernel: K-contiguous A, three B planes, row-major C only,
-    // no column maxima or scales
-    if (a_mcontig || c_trans || cmax != nullptr || planesB != 3 || nscale != nullptr) return hipErrorInvalidValue;
-    const int vec = (lda % 8 == 0) && (ldb % 8 == 0) && (planeStride % 8 == 0) &&
-                    (batch == 1 || (strideA % 8 == 0 && strideB % 8 == 0)) &&
-                    (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(Bplanes) % 16 == 0);
-    dim3 grid((N + XN - 1) / XN, (M + XM - 1) / XM, batch);
-    hipLaunchKernelGGL(gemm_bf16x3_kernel, grid, dim3(XT), 0, stream, g, vec);
-    return hipGetLastError();
 }
 
 hipError_t launch_split3_rows(const float* src, int64_t lds, int64_t strideS, void* planes, int64_t ldp,

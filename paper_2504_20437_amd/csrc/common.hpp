@@ -116,11 +116,9 @@ hipError_t launch_gemm(ALayout la, BLayout lb, bool a_bf16, bool b_bf16, const G
 
 hipError_t launch_sketch(float* omega, int64_t l, int64_t k, int64_t stride, uint64_t seed,
                          uint64_t sketch_index0, int batch, hipStream_t stream);
-// the sketch as the one bf16 plane of Omega^T (k rows of ldp, zero past l);
-// zero_rest also zeroes the next two planes
-hipError_t launch_sketch_plane(uint16_t* planes, int64_t ldp, int64_t planeStride, int64_t stride, int64_t l,
-                               int64_t k, uint64_t seed, uint64_t sketch_index0, bool zero_rest, int batch,
-                               hipStream_t stream);
+// the sketch as the one bf16 plane of Omega^T (k rows of ldp, zero past l)
+hipError_t launch_sketch_plane(uint16_t* planes, int64_t ldp, int64_t stride, int64_t l, int64_t k, uint64_t seed,
+                               uint64_t sketch_index0, int batch, hipStream_t stream);
 
 // Cholesky of the k x k fp64 Gram (in place, upper factor R in the upper
 // triangle). xinv (k x k fp64) receives the inverses of the diagonal blocks
@@ -214,8 +212,9 @@ hipError_t launch_copy_rows(const float* src, int64_t lds, int64_t strideS, floa
                             int64_t strideD, int rows, int cols, int batch, hipStream_t stream);
 
 // bf16 matrix-core products with an exactly bf16 operand (bf16x3.hip)
-hipError_t launch_transpose_bf16(const void* src, int64_t lds, int64_t strideS, void* dst, int64_t ldd,
-                                 int64_t strideD, int rows, int cols, int batch, hipStream_t stream);
+// copy of a bf16 matrix with zero rows and columns up to rows_pad x ldd
+hipError_t launch_pad_bf16(const void* src, int64_t lds, int64_t strideS, void* dst, int64_t ldd, int64_t strideD,
+                           int rows, int cols, int rows_pad, int batch, hipStream_t stream);
 hipError_t launch_split3_transpose(const float* src, int64_t lds, int64_t strideS, void* planes, int64_t ldp,
                                    int64_t planeStride, int64_t strideP, int rows, int cols, int rows_pad,
                                    int batch, hipStream_t stream, const float* rowscale = nullptr,
@@ -223,18 +222,17 @@ hipError_t launch_split3_transpose(const float* src, int64_t lds, int64_t stride
 // C (M x N, or its transpose when c_trans) = alpha A B + beta C with A bf16
 // (rows K-contiguous, A[i * lda + kk], or M-contiguous when a_mcontig,
 // A[kk * lda + i]) and B given as three bf16 planes, each N x K rows.
-// M-contiguous A and transposed C need the direct-load kernel: check
-// bf16x3_direct_ok first (hipErrorInvalidValue otherwise).
+// hipErrorInvalidValue unless bf16x3_direct_ok (M there, for an M-contiguous A,
+// the entries of a row that may be loaded: mload, at least M; 0: M).
 bool bf16x3_direct_ok(const void* A, int64_t lda, int64_t strideA, const void* Bplanes, int64_t ldb,
                       int64_t planeStride, int64_t strideB, int M, int K, int batch, int a_mcontig);
-// cmax (row-major C on the direct-load kernel only, else hipErrorInvalidValue):
-// per matrix strideCM unsigned, atomicMax'ed with the bits of |C| per column
+// cmax (row-major C only): per matrix strideCM unsigned, atomicMax'ed with the bits of |C| per column
 // (the caller zeroes it first); null for none.
 hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a_mcontig, const void* Bplanes,
                               int64_t ldb, int64_t planeStride, int64_t strideB, float* C, int64_t ldc,
                               int64_t strideC, int c_trans, int M, int N, int K, float alpha, float beta, int batch,
                               hipStream_t stream, unsigned* cmax = nullptr, int64_t strideCM = 0, int planesB = 3,
-                              const float* nscale = nullptr, int64_t strideNS = 0);
+                              const float* nscale = nullptr, int64_t strideNS = 0, int mload = 0);
 
 // fp32 x fp32 products on the bf16 matrix cores: both operands given as three
 // bf16 planes with K-contiguous rows (A: M rows, B: N rows), six plane products

@@ -69,11 +69,11 @@ struct Layout {
     size_t offL1, offL2, offS1, offS2, offC, offXinv, offRinv, offYt, offUr, offDef, offDiag0, offRot,
         offJexp, offTheta, offXb, offS, offGg, offLam, offFlags, offNorm, offPerm;
     int64_t strideTheta;
-    // bf16-stored gradients only: transposed copy of G (n x ldgt) and three
-    // bf16 planes of the split fp32 operand (k x ldpl each)
+    // bf16-stored gradients only: padded copy of G (GradPad) and three bf16
+    // planes of the split fp32 operand (k x ldpl each)
     bool bf16;
-    int64_t ldgt, strideGt, ldpl, planeStride, stridePl;
-    size_t offGt, offPl;
+    int64_t strideGp, ldpl, planeStride, stridePl;
+    size_t offGp, offPl;
     // digit planes and column maxima of the exact int8 Gram
     int64_t strideQ, strideCM;
     size_t offQ, offCM;
@@ -81,6 +81,17 @@ struct Layout {
 };
 
 int64_t pad8(int64_t x) { return (x + 7) / 8 * 8; }
+int64_t pad32(int64_t x) { return (x + 31) / 32 * 32; }
+
+// A bf16 gradient copied with both sides padded to multiples of 32 by zeros:
+// rows 16-byte aligned and contractions of whole stages for the direct-load
+// products, whatever G's own sizes, row pitch and alignment. (8 x 2048x5461: the
+// copy takes 63 us, a product 300 us against 1830 us through registers with
+// two-byte loads, the projection 365 us against 1450 us on the fp32 cores.)
+struct GradPad {
+    int64_t rows, ld, stride;
+    explicit GradPad(const Shape& sh) : rows(pad32(sh.m)), ld(pad32(sh.n)), stride(pad_elems(rows * ld)) {}
+};
 
 Layout make_layout(const Shape& sh, int r, int batch, bool bf16) {
     Layout L;
@@ -124,12 +135,11 @@ Layout make_layout(const Shape& sh, int r, int batch, bool bf16) {
     L.strideTheta = 2 * pad_elems(2 * k + r);
     L.offTheta = take(B * L.strideTheta * sizeof(float));
     L.bf16 = bf16;
-    L.ldgt = pad8(sh.m);
-    L.strideGt = pad_elems(sh.n * L.ldgt);
-    L.ldpl = pad8(sh.l);
+    L.strideGp = GradPad(sh).stride;
+    L.ldpl = pad32(sh.l);
     L.planeStride = pad_elems(k * L.ldpl);
     L.stridePl = 3 * L.planeStride;
-    L.offGt = bf16 ? take(B * L.strideGt * sizeof(uint16_t)) : 0;
+    L.offGp = bf16 ? take(B * L.strideGp * sizeof(uint16_t)) : 0;
     L.offPl = bf16 ? take(B * L.stridePl * sizeof(uint16_t)) : 0;
     L.strideQ = static_cast<int64_t>(align_up(gram_i8_digit_bytes(static_cast<int>(sh.l), sh.k), kAlign));
     L.strideCM = pad_elems(k);
@@ -197,24 +207,24 @@ hipError_t gemm_At_times(const Shape& sh, const GradOp& g, const float* Q, int64
 // The products of the subspace update with the gradient. For fp32 G they run
 // on the fp32 matrix cores reading G in place; for bf16 G the fp32 operand is
 // split into three bf16 planes and the product runs on the bf16 matrix cores
-// (bf16x3.hip) with the rows of A (G or its transposed copy) K-contiguous.
+// (bf16x3.hip), G (or its padded copy) read in place in both orientations.
 struct Products {
     const Shape* sh;
     const Layout* L;
-    GradOp g;
-    uint16_t* gt;       // transposed copy of G, n x ldgt (bf16 path without direct loads)
+    GradOp g;           // bf16 path: G itself or its padded copy
     uint16_t* planes;   // split planes (bf16 path)
-    bool direct;        // bf16: both products read G in place (direct-load kernel)
+    int ks, kl;         // bf16 path: the s and l sides as contractions (multiples of 32)
+    int gcols;          // bf16 path: row length of g, padding included
     int batch;
     hipStream_t st;
-    unsigned* cmax;     // column maxima of the product for the next Gram (direct-load kernel only)
+    unsigned* cmax;     // column maxima of the product for the next Gram (bf16 path only)
     int64_t strideCM;
 };
 
 // Zero the column-maximum buffer for a product that fills it; false when the
 // product cannot (its Gram then takes the maxima itself).
 bool cmax_prepare(const Products& P) {
-    if (!P.direct || P.cmax == nullptr) return false;
+    if (!P.L->bf16 || P.cmax == nullptr) return false;
     return launch_fill_u32(P.cmax, P.strideCM * P.batch, P.st) == hipSuccess;
 }
 
@@ -294,8 +304,7 @@ struct Tracer {
     } while (0)
 
 // Y (s x k) = A X, X (l x k). With planes1 (bf16 G only) X is not read: the
-// planes already hold X^T as one bf16 plane (exact), two more zero planes when
-// the product cannot read G in place.
+// first plane already holds X^T as bf16 (exact).
 int product_A(const Products& P, Tracer& tr, const float* X, int64_t strideX, float* Y, int64_t strideY,
               bool& cmax_ready, bool planes1 = false, bool planes_ready = false) {
     const Shape& sh = *P.sh;
@@ -308,20 +317,14 @@ int product_A(const Products& P, Tracer& tr, const float* X, int64_t strideX, fl
     const int k = sh.k, s = static_cast<int>(sh.s), l = static_cast<int>(sh.l);
     if (!planes1 && !planes_ready)
         GALORE_TRACED(tr, GALORE_STAGE_OPERAND,
-                      launch_split3_transpose(X, k, strideX, P.planes, L.ldpl, L.planeStride, L.stridePl, l, k,
-                                              static_cast<int>(L.ldpl), P.batch, P.st));
-    // left: A = G (K-contiguous); right: A = G^T, read in place (M-contiguous)
-    // or from the transposed copy
-    const bool inplace = sh.left || P.direct;
-    const void* A = inplace ? P.g.G : static_cast<const void*>(P.gt);
-    const int64_t lda = inplace ? P.g.ldg : L.ldgt;
-    const int64_t strideA = inplace ? P.g.stride : L.strideGt;
+                      launch_split3_transpose(X, k, strideX, P.planes, L.ldpl, L.planeStride, L.stridePl, l, k, P.kl,
+                                              P.batch, P.st));
+    // left: A = G (K-contiguous); right: A = G^T (M-contiguous)
     cmax_ready = cmax_prepare(P);
     GALORE_TRACED(tr, GALORE_STAGE_PRODUCT_A,
-                  launch_gemm_bf16x3(A, lda, strideA, sh.left ? 0 : (P.direct ? 1 : 0), P.planes, L.ldpl,
-                                     L.planeStride, L.stridePl, Y, k, strideY, 0, s, k, l, 1.0f, 0.0f, P.batch,
-                                     P.st, cmax_ready ? P.cmax : nullptr, P.strideCM,
-                                     (planes1 && P.direct) ? 1 : 3));
+                  launch_gemm_bf16x3(P.g.G, P.g.ldg, P.g.stride, sh.left ? 0 : 1, P.planes, L.ldpl, L.planeStride,
+                                     L.stridePl, Y, k, strideY, 0, s, k, P.kl, 1.0f, 0.0f, P.batch, P.st,
+                                     cmax_ready ? P.cmax : nullptr, P.strideCM, planes1 ? 1 : 3, nullptr, 0, P.gcols));
     return GALORE_OK;
 }
 
@@ -338,19 +341,14 @@ int product_At(const Products& P, Tracer& tr, const float* Q, int64_t strideQ, f
     const int k = sh.k, s = static_cast<int>(sh.s), l = static_cast<int>(sh.l);
     if (!planes_ready)
         GALORE_TRACED(tr, GALORE_STAGE_OPERAND,
-                      launch_split3_transpose(Q, k, strideQ, P.planes, L.ldpl, L.planeStride, L.stridePl, s, k,
-                                              static_cast<int>(pad8(s)), P.batch, P.st));
-    // left: A^T = G^T, read in place (M-contiguous) or from the transposed
-    // copy; right: A^T = G (K-contiguous)
-    const bool inplace = !sh.left || P.direct;
-    const void* At = inplace ? P.g.G : static_cast<const void*>(P.gt);
-    const int64_t ldat = inplace ? P.g.ldg : L.ldgt;
-    const int64_t strideAt = inplace ? P.g.stride : L.strideGt;
+                      launch_split3_transpose(Q, k, strideQ, P.planes, L.ldpl, L.planeStride, L.stridePl, s, k, P.ks,
+                                              P.batch, P.st));
+    // left: A^T = G^T (M-contiguous); right: A^T = G (K-contiguous)
     cmax_ready = cmax_prepare(P);
     GALORE_TRACED(tr, GALORE_STAGE_PRODUCT_AT,
-                  launch_gemm_bf16x3(At, ldat, strideAt, sh.left ? (P.direct ? 1 : 0) : 0, P.planes, L.ldpl,
-                                     L.planeStride, L.stridePl, Z, k, strideZ, 0, l, k, s, 1.0f, 0.0f, P.batch,
-                                     P.st, cmax_ready ? P.cmax : nullptr, P.strideCM));
+                  launch_gemm_bf16x3(P.g.G, P.g.ldg, P.g.stride, sh.left ? 1 : 0, P.planes, L.ldpl, L.planeStride,
+                                     L.stridePl, Z, k, strideZ, 0, l, k, P.ks, 1.0f, 0.0f, P.batch, P.st,
+                                     cmax_ready ? P.cmax : nullptr, P.strideCM, 3, nullptr, 0, P.gcols));
     return GALORE_OK;
 }
 
@@ -496,30 +494,35 @@ int rsvd_impl(const void* G, int32_t g_dtype, int64_t m, int64_t n, int64_t ldg,
     float* Sa = w.f(L.offS1);
     float* Sb = w.f(L.offS2);
 
-    Products prod{&sh, &L, gop, L.bf16 ? reinterpret_cast<uint16_t*>(w.base + L.offGt) : nullptr,
-                  L.bf16 ? reinterpret_cast<uint16_t*>(w.base + L.offPl) : nullptr, false, batch, stream,
-                  reinterpret_cast<unsigned*>(w.base + L.offCM), L.strideCM};
+    Products prod{&sh, &L, gop, L.bf16 ? reinterpret_cast<uint16_t*>(w.base + L.offPl) : nullptr, s, l,
+                  static_cast<int>(n), batch, stream, reinterpret_cast<unsigned*>(w.base + L.offCM), L.strideCM};
     bool ready = false;   // the last product left the column maxima of its output
     if (L.bf16) {
-        // both products read G in place when the direct-load kernel takes them:
-        // G rows are K-contiguous for one product and M-contiguous for the other
+        // both products read G in place when the direct-load kernel takes it (G
+        // rows are K-contiguous for one and M-contiguous for the other), else
+        // its padded copy
         const bool kc_ok = bf16x3_direct_ok(G, ldg, stride_g, prod.planes, L.ldpl, L.planeStride, L.stridePl,
                                             static_cast<int>(m), static_cast<int>(n), batch, 0);
         const bool mc_ok = bf16x3_direct_ok(G, ldg, stride_g, prod.planes, L.ldpl, L.planeStride, L.stridePl,
                                             static_cast<int>(n), static_cast<int>(m), batch, 1);
-        prod.direct = kc_ok && mc_ok;
-        if (!prod.direct)   // A^T (left) or A (right) as K-contiguous bf16 rows: G^T, n x m
+        if (!(kc_ok && mc_ok)) {
+            const GradPad gp(sh);
+            uint16_t* copy = reinterpret_cast<uint16_t*>(w.base + L.offGp);
             GALORE_TRACED(tr, GALORE_STAGE_OPERAND,
-                          launch_transpose_bf16(G, ldg, stride_g, prod.gt, L.ldgt, L.strideGt, static_cast<int>(m),
-                                                static_cast<int>(n), batch, stream));
+                          launch_pad_bf16(G, ldg, stride_g, copy, gp.ld, gp.stride, static_cast<int>(m),
+                                          static_cast<int>(n), static_cast<int>(gp.rows), batch, stream));
+            prod.g = GradOp{copy, true, gp.ld, gp.stride};
+            prod.ks = static_cast<int>(pad32(s));
+            prod.kl = static_cast<int>(pad32(l));
+            prod.gcols = static_cast<int>(gp.ld);
+        }
     }
 
     // a1-a3: sketch, range sample, orthonormalise (a bf16 G takes the sketch as
     // the bf16 plane of its transpose: one exact bf16 product)
     if (L.bf16)
         GALORE_TRACED(tr, GALORE_STAGE_SKETCH,
-                      launch_sketch_plane(prod.planes, L.ldpl, L.planeStride, L.stridePl, l, k, seed, sketch_index0,
-                                          !prod.direct, batch, stream));
+                      launch_sketch_plane(prod.planes, L.ldpl, L.stridePl, l, k, seed, sketch_index0, batch, stream));
     else
         GALORE_TRACED(tr, GALORE_STAGE_SKETCH, launch_sketch(L1, l, k, L.strideL, seed, sketch_index0, batch, stream));
     GALORE_CHECK(product_A(prod, tr, L1, L.strideL, Sa, L.strideS, ready, L.bf16));
@@ -528,8 +531,8 @@ int rsvd_impl(const void* G, int32_t g_dtype, int64_t m, int64_t n, int64_t ldg,
     // with a bf16 G an orthonormal panel that only feeds the next product is
     // written by Y R^-1 straight as that product's three bf16 planes (the same
     // bits the split of its fp32 values gives), and never in fp32
-    const PlaneOut po_s{prod.planes, L.ldpl, L.planeStride, L.stridePl, static_cast<int>(pad8(s))};
-    const PlaneOut po_l{prod.planes, L.ldpl, L.planeStride, L.stridePl, static_cast<int>(L.ldpl)};
+    const PlaneOut po_s{prod.planes, L.ldpl, L.planeStride, L.stridePl, prod.ks};
+    const PlaneOut po_l{prod.planes, L.ldpl, L.planeStride, L.stridePl, prod.kl};
     bool q_planes = false;   // Q exists only as the planes of the next product
     auto orth_s = [&](int passes) -> int {
         for (int ps = 0; ps < passes; ++ps) {
@@ -782,18 +785,30 @@ int galore_svd_update(const void* G, int32_t g_dtype, int64_t m, int64_t n, int6
 }
 
 // Workspace of the projection with a bf16 gradient: the three bf16 planes of
-// P^T (r x pad8(s) each) per matrix.
+// P^T (r x pad8(s) each) per matrix; for a G whose rows, packed, the direct-load
+// product cannot take (copy), planes padded to 32 and the padded copy of G as
+// well. A workspace of the first size alone still serves (without the copy).
 struct ProjLayout {
     int64_t ldpl, planeStride, stridePl;
     size_t total;
+    bool copy;
+    int64_t ldplC, planeStrideC, strideGp;
+    size_t offGp, totalC;
 };
 
-ProjLayout make_proj_layout(const Shape& sh, int r, int batch) {
+// planes: 3 (fp32 P) or 1 (codes)
+ProjLayout make_proj_layout(const Shape& sh, int r, int batch, int planes = 3) {
     ProjLayout pl;
     pl.ldpl = pad8(sh.s);
     pl.planeStride = pad_elems(static_cast<int64_t>(r) * pl.ldpl);
-    pl.stridePl = 3 * pl.planeStride;
+    pl.stridePl = planes * pl.planeStride;
     pl.total = align_up(static_cast<size_t>(batch) * pl.stridePl * sizeof(uint16_t), kAlign);
+    pl.copy = sh.s % 32 != 0 || sh.n % 8 != 0;
+    pl.ldplC = pad32(sh.s);
+    pl.planeStrideC = pad_elems(static_cast<int64_t>(r) * pl.ldplC);
+    pl.strideGp = GradPad(sh).stride;
+    pl.offGp = align_up(static_cast<size_t>(batch) * planes * pl.planeStrideC * sizeof(uint16_t), kAlign);
+    pl.totalC = pl.offGp + align_up(static_cast<size_t>(batch) * pl.strideGp * sizeof(uint16_t), kAlign);
     return pl;
 }
 
@@ -802,7 +817,8 @@ size_t galore_project_workspace_size(int64_t m, int64_t n, int32_t r, int32_t ba
     if (g_dtype != GALORE_BF16) return 0;
     const Shape sh = make_shape(m, n, r, 0);
     if (r > sh.s) return 0;
-    return make_proj_layout(sh, r, batch).total;
+    const ProjLayout pl = make_proj_layout(sh, r, batch);
+    return pl.copy ? std::max(pl.total, pl.totalC) : pl.total;
 }
 
 int galore_project(const float* P, int64_t ldp, int64_t stride_p, const void* G, int32_t g_dtype,
@@ -832,6 +848,21 @@ int galore_project(const float* P, int64_t ldp, int64_t stride_p, const void* G,
             GALORE_TRY(launch_gemm_bf16x3(G, ldg, stride_g, a_mc, planes, pl.ldpl, pl.planeStride, pl.stridePl, R,
                                           ldr, stride_r, 1, static_cast<int>(sh.l), r, static_cast<int>(sh.s),
                                           1.0f, 0.0f, batch, stream));
+            return GALORE_OK;
+        }
+        if (pl.copy && workspace_bytes >= pl.totalC) {
+            const GradPad gp(sh);
+            const int ks = static_cast<int>(pl.ldplC);
+            uint16_t* copy = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + pl.offGp);
+            GALORE_TRY(launch_pad_bf16(G, ldg, stride_g, copy, gp.ld, gp.stride, static_cast<int>(m),
+                                       static_cast<int>(n), static_cast<int>(gp.rows), batch, stream));
+            GALORE_TRY(launch_split3_transpose(P, ldp, (batch > 1) ? stride_p : sh.s * ldp, planes, pl.ldplC,
+                                               pl.planeStrideC, 3 * pl.planeStrideC, static_cast<int>(sh.s), r, ks,
+                                               batch, stream));
+            GALORE_TRY(launch_gemm_bf16x3(copy, gp.ld, gp.stride, a_mc, planes, pl.ldplC, pl.planeStrideC,
+                                          3 * pl.planeStrideC, R, ldr, stride_r, 1, static_cast<int>(sh.l), r, ks,
+                                          1.0f, 0.0f, batch, stream, nullptr, 0, 3, nullptr, 0,
+                                          static_cast<int>(gp.ld)));
             return GALORE_OK;
         }
     }
@@ -872,12 +903,11 @@ int galore_project_noalloc(const float* P, int64_t ldp, int64_t stride_p, const 
     if (g_dtype == GALORE_F32)   // the fp32 path needs no scratch
         return galore_project(P, ldp, stride_p, G, g_dtype, m, n, ldg, stride_g, r, R, ldr, stride_r, batch, nullptr,
                               0, stream);
-    const size_t need = make_proj_layout(sh, r, batch).total;
-    if (need > kStaticScratchBytes) return GALORE_ERR_WORKSPACE;
+    if (make_proj_layout(sh, r, batch).total > kStaticScratchBytes) return GALORE_ERR_WORKSPACE;
     void* ws = scratch_on_current_device();
     if (ws == nullptr) return GALORE_ERR_HIP;
-    return galore_project(P, ldp, stride_p, G, g_dtype, m, n, ldg, stride_g, r, R, ldr, stride_r, batch, ws, need,
-                          stream);
+    return galore_project(P, ldp, stride_p, G, g_dtype, m, n, ldg, stride_g, r, R, ldr, stride_r, batch, ws,
+                          kStaticScratchBytes, stream);
 }
 
 size_t galore_align_workspace_size(int32_t r, int32_t batch) {
@@ -1122,7 +1152,10 @@ QuantLayout make_quant_layout(const Shape& sh, int r, int batch, bool back) {
 
 size_t galore_project_quantized_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch) {
     if (m < 1 || n < 1 || r < 1 || batch < 1 || m > INT32_MAX || n > INT32_MAX || r > std::min(m, n)) return 0;
-    return make_quant_layout(make_shape(m, n, r, 0), r, batch, false).total;
+    const Shape sh = make_shape(m, n, r, 0);
+    const ProjLayout pl = make_proj_layout(sh, r, batch, 1);
+    const size_t total = make_quant_layout(sh, r, batch, false).total;
+    return pl.copy ? std::max(total, pl.totalC) : total;
 }
 
 size_t galore_project_back_quantized_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch) {
@@ -1159,6 +1192,20 @@ int galore_project_quantized(const uint8_t* Q, int64_t ldq, int64_t stride_q, co
             GALORE_TRY(launch_gemm_bf16x3(G, ldg, stride_g, a_mc, plane, ql.ldpl, 0, ql.plane, R, ldr, stride_r, 1,
                                           static_cast<int>(sh.l), r, static_cast<int>(sh.s), 1.0f, 0.0f, batch,
                                           stream, nullptr, 0, 1, scales, ss));
+            return GALORE_OK;
+        }
+        const ProjLayout pl = make_proj_layout(sh, r, batch, 1);
+        if (pl.copy && workspace_bytes >= pl.totalC) {
+            const GradPad gp(sh);
+            const int ks = static_cast<int>(pl.ldplC);
+            uint16_t* copy = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + pl.offGp);
+            GALORE_TRY(launch_pad_bf16(G, ldg, stride_g, copy, gp.ld, gp.stride, static_cast<int>(m),
+                                       static_cast<int>(n), static_cast<int>(gp.rows), batch, stream));
+            GALORE_TRY(launch_codes_plane(Q, ldq, sq, bits, static_cast<int>(sh.s), r, plane, pl.ldplC,
+                                          pl.planeStrideC, ks, true, batch, stream));
+            GALORE_TRY(launch_gemm_bf16x3(copy, gp.ld, gp.stride, a_mc, plane, pl.ldplC, 0, pl.planeStrideC, R, ldr,
+                                          stride_r, 1, static_cast<int>(sh.l), r, ks, 1.0f, 0.0f, batch, stream,
+                                          nullptr, 0, 1, scales, ss, static_cast<int>(gp.ld)));
             return GALORE_OK;
         }
     }

@@ -113,10 +113,10 @@ __global__ __launch_bounds__(256) void sketch_kernel(float* omega, int64_t l, in
 }
 
 // the bf16 plane of Omega^T: plane[j][i] = Omega[i][j] (k rows of ldp, zero for
-// l <= i < ldp); with zero_rest the next two planes (at planeStride) are zeroed
-__global__ __launch_bounds__(256) void sketch_plane_kernel(uint16_t* planes, int64_t ldp, int64_t planeStride,
-                                                           int64_t stride, int64_t l, int64_t k, uint64_t seed,
-                                                           uint64_t sketch_index0, int zero_rest) {
+// l <= i < ldp)
+__global__ __launch_bounds__(256) void sketch_plane_kernel(uint16_t* planes, int64_t ldp, int64_t stride,
+                                                           int64_t l, int64_t k, uint64_t seed,
+                                                           uint64_t sketch_index0) {
     const int b = blockIdx.y;
     uint16_t* pl = planes + static_cast<int64_t>(b) * stride;
     const uint64_t sidx = sketch_index0 + static_cast<uint64_t>(b);
@@ -138,27 +138,21 @@ __global__ __launch_bounds__(256) void sketch_plane_kernel(uint16_t* planes, int
         }
         const int64_t o = j * ldp + 4 * i4;
         *reinterpret_cast<uint2*>(pl + o) = v;
-        if (zero_rest) {
-            *reinterpret_cast<uint2*>(pl + planeStride + o) = make_uint2(0u, 0u);
-            *reinterpret_cast<uint2*>(pl + 2 * planeStride + o) = make_uint2(0u, 0u);
-        }
     }
 }
 
 }  // namespace
 
-hipError_t launch_sketch_plane(uint16_t* planes, int64_t ldp, int64_t planeStride, int64_t stride, int64_t l,
-                               int64_t k, uint64_t seed, uint64_t sketch_index0, bool zero_rest, int batch,
-                               hipStream_t stream) {
-    if (ldp % 4 != 0 || ldp < l || planeStride % 4 != 0 || stride % 4 != 0 ||
-        reinterpret_cast<uintptr_t>(planes) % 8 != 0)
+hipError_t launch_sketch_plane(uint16_t* planes, int64_t ldp, int64_t stride, int64_t l, int64_t k, uint64_t seed,
+                               uint64_t sketch_index0, int batch, hipStream_t stream) {
+    if (ldp % 4 != 0 || ldp < l || stride % 4 != 0 || reinterpret_cast<uintptr_t>(planes) % 8 != 0)
         return hipErrorInvalidValue;
     const int64_t total = k * (ldp / 4);
     int64_t blocks = (total + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     dim3 grid(static_cast<unsigned>(blocks), batch);
-    hipLaunchKernelGGL(sketch_plane_kernel, grid, dim3(256), 0, stream, planes, ldp, planeStride, stride, l, k, seed,
-                       sketch_index0, zero_rest ? 1 : 0);
+    hipLaunchKernelGGL(sketch_plane_kernel, grid, dim3(256), 0, stream, planes, ldp, stride, l, k, seed,
+                       sketch_index0);
     return hipGetLastError();
 }
 

@@ -1056,3 +1056,50 @@ def test_rsvd_cholesky_block_edges(gl, orc, k):
         assert orth_err(P) < 1e-4
         assert max_rel_violation(sig[:rank], ss[:rank], 1e-4, 1e-30) <= 1.0
         assert np.all(sig[rank:] <= 1e-4 * sig[0])
+
+
+@pytest.mark.parametrize("m,n,ldg,off,r,bits", [(33, 47, 47, 0, 8, 8), (64, 96, 97, 1, 16, 4), (96, 65, 65, 0, 32, 8),
+                                                (31, 300, 301, 3, 7, 8), (257, 40, 45, 1, 33, 4), (128, 264, 272, 5, 32, 8)])
+def test_unaligned_bf16_gradient(gl, orc, m, n, ldg, off, r, bits):
+    """bf16 gradients whose rows start on no 16-byte boundary, by size, by row
+    pitch or by the pointer, both orientations: the update, the projection and
+    the low-bit projection through the padded copy, which holds zeros past the
+    matrix (the memory beside G holds NaN), and the projection with a workspace of
+    the planes alone."""
+    import torch
+    s, l = min(m, n), max(m, n)
+    # sigma's error is of order 2^-24 sigma_1 / sigma_i relative (fp32 products): with
+    # 0.9^32 = 0.03 that is 2e-6, far under 1e-4 (0.8^32 = 8e-4 would leave 1e-4 itself)
+    spec = gi.spectrum_gapped(gi.spectrum_geometric(s, 0.9), r)
+    G = [gi.store(gi.planted_gradient(m, n, spec, 1e-6, seed=m + n + i), "bf16") for i in range(2)]
+    buf = torch.full((2 * m * ldg + off + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Gd = torch.as_strided(buf, (2, m, n), (m * ldg, ldg, 1), off)
+    for i in range(2):
+        Gd[i].copy_(dev_stored(G[i]))
+    P, sig, info = gl.galore_rsvd_update(Gd, r, 4, 2, 3)
+    assert (info.cpu().numpy() == 0).all()
+    R = gl.galore_project(P, Gd)
+    base = 256 * ((2 * 3 * 64 * ((r * ((s + 7) // 8 * 8) + 63) // 64) * 2 + 255) // 256)
+    R0 = gl.galore_project(P, Gd, workspace=torch.empty((base,), dtype=torch.uint8, device="cuda"))
+    Pq = gl.galore_quantize_projector(P, bits)
+    Rq = gl.galore_project_quantized(Pq, Gd)
+    for i in range(2):
+        A = G[i].exact if m <= n else G[i].exact.T
+        Pr, sr, _ = orc.rsvd_update(G[i].exact, r, 4, 2, 3, i)
+        assert proj_dist(host(P)[i], Pr) <= 1e-3
+        assert max_rel_violation(host(sig)[i], sr, 1e-4, 1e-30) <= 1.0
+        Pi = host(P)[i]
+        # fp32 accumulation of s products: s 2^-24 of the sum of their sizes, and more than its few ulps
+        bound = (s * 2.0 ** -24 + 2.0 ** -22) * (np.abs(Pi).T @ np.abs(A))
+        for x in (R, R0):
+            assert np.all(np.abs(host(x)[i] - Pi.T @ A) <= bound)
+        codes = Pq.codes[i].cpu().numpy()
+        if bits == 4:
+            lo, hi = (codes & 15).astype(np.int8), (codes >> 4).astype(np.int8)
+            c = np.stack([lo, hi], axis=2).reshape(s, -1)[:, :r]
+            c = np.where(c > 7, c - 16, c)
+        else:
+            c = codes.view(np.int8)
+        Pqi = c.astype(np.float64) * Pq.scales[i].cpu().numpy().astype(np.float64)
+        bound = (s * 2.0 ** -24 + 2.0 ** -22) * (np.abs(Pqi).T @ np.abs(A))
+        assert np.all(np.abs(host(Rq)[i] - Pqi.T @ A) <= bound)
