@@ -87,6 +87,10 @@ struct GemmArgs {
     uint16_t* planes;
     int64_t ldpl, planeStride, stridePl;
     int rows_pad;
+    // cmax != nullptr (not with planes): per matrix strideCM unsigned, atomicMax'ed
+    // with the bits of |C| per column (the caller zeroes it first)
+    unsigned* cmax;
+    int64_t strideCM;
 };
 
 // Exact Gram of the fixed-point image of X on the int8 matrix cores (gram_i8.hip):

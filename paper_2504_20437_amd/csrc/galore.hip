@@ -160,8 +160,10 @@ struct GradOp {
 
 // Y (s x k, ld k) = A X, X (l x k, ld k)
 hipError_t gemm_A_times(const Shape& sh, const GradOp& g, const float* X, int64_t strideX, float* Y,
-                        int64_t strideY, int batch, hipStream_t st) {
+                        int64_t strideY, int batch, hipStream_t st, unsigned* cmax, int64_t strideCM) {
     GemmArgs a{};
+    a.cmax = cmax;
+    a.strideCM = strideCM;
     a.A = g.G;
     a.lda = g.ldg;
     a.strideA = g.stride;
@@ -183,8 +185,10 @@ hipError_t gemm_A_times(const Shape& sh, const GradOp& g, const float* X, int64_
 
 // Z (l x k, ld k) = A^T Q, Q (s x k, ld k)
 hipError_t gemm_At_times(const Shape& sh, const GradOp& g, const float* Q, int64_t strideQ, float* Z,
-                         int64_t strideZ, int batch, hipStream_t st) {
+                         int64_t strideZ, int batch, hipStream_t st, unsigned* cmax, int64_t strideCM) {
     GemmArgs a{};
+    a.cmax = cmax;
+    a.strideCM = strideCM;
     a.A = g.G;
     a.lda = g.ldg;
     a.strideA = g.stride;
@@ -217,15 +221,14 @@ struct Products {
     int gcols;          // bf16 path: row length of g, padding included
     int batch;
     hipStream_t st;
-    unsigned* cmax;     // column maxima of the product for the next Gram (bf16 path only)
+    unsigned* cmax;     // column maxima of the product for the next Gram
     int64_t strideCM;
 };
 
-// Zero the column-maximum buffer for a product that fills it; false when the
-// product cannot (its Gram then takes the maxima itself).
+// Zero the column-maximum buffer for a product that fills it; false where that
+// fails (the Gram then takes the maxima itself).
 bool cmax_prepare(const Products& P) {
-    if (!P.L->bf16 || P.cmax == nullptr) return false;
-    return launch_fill_u32(P.cmax, P.strideCM * P.batch, P.st) == hipSuccess;
+    return P.cmax != nullptr && launch_fill_u32(P.cmax, P.strideCM * P.batch, P.st) == hipSuccess;
 }
 
 // Three bf16 planes that a product's epilogue writes in place of its fp32
@@ -309,9 +312,11 @@ int product_A(const Products& P, Tracer& tr, const float* X, int64_t strideX, fl
               bool& cmax_ready, bool planes1 = false, bool planes_ready = false) {
     const Shape& sh = *P.sh;
     const Layout& L = *P.L;
-    cmax_ready = false;
     if (!L.bf16) {
-        GALORE_TRACED(tr, GALORE_STAGE_PRODUCT_A, gemm_A_times(sh, P.g, X, strideX, Y, strideY, P.batch, P.st));
+        cmax_ready = cmax_prepare(P);
+        GALORE_TRACED(tr, GALORE_STAGE_PRODUCT_A,
+                      gemm_A_times(sh, P.g, X, strideX, Y, strideY, P.batch, P.st, cmax_ready ? P.cmax : nullptr,
+                                   P.strideCM));
         return GALORE_OK;
     }
     const int k = sh.k, s = static_cast<int>(sh.s), l = static_cast<int>(sh.l);
@@ -333,9 +338,11 @@ int product_At(const Products& P, Tracer& tr, const float* Q, int64_t strideQ, f
                bool& cmax_ready, bool planes_ready = false) {
     const Shape& sh = *P.sh;
     const Layout& L = *P.L;
-    cmax_ready = false;
     if (!L.bf16) {
-        GALORE_TRACED(tr, GALORE_STAGE_PRODUCT_AT, gemm_At_times(sh, P.g, Q, strideQ, Z, strideZ, P.batch, P.st));
+        cmax_ready = cmax_prepare(P);
+        GALORE_TRACED(tr, GALORE_STAGE_PRODUCT_AT,
+                      gemm_At_times(sh, P.g, Q, strideQ, Z, strideZ, P.batch, P.st, cmax_ready ? P.cmax : nullptr,
+                                    P.strideCM));
         return GALORE_OK;
     }
     const int k = sh.k, s = static_cast<int>(sh.s), l = static_cast<int>(sh.l);

@@ -5,8 +5,9 @@
 //    v_mfma_f32_32x32x2_f32. gfx950 has no TF32 matrix path, so fp32 MFMA is
 //    the precision the method is computed in. bf16-stored gradients are
 //    widened exactly to fp32 while staging into LDS.
-//    Workgroup tile 128 x 128 x 32, four wave64s in a 2 x 2 arrangement, each
-//    wave owning a 64 x 64 sub-tile (2 x 2 MFMA 32x32 blocks). LDS holds A^T
+//    Workgroup tile 128 x 128 x 32 (or 64 x 64 x 64 for launches of few tiles),
+//    four wave64s in a 2 x 2 arrangement, each wave owning a 64 x 64 (32 x 32)
+//    sub-tile (2 x 2 MFMA 32x32 blocks, or one). LDS holds A^T
 //    and B tiles in M-/N-contiguous order so that the per-lane MFMA operand
 //    reads are consecutive addresses; double-buffered with one barrier per
 //    K step, the next tile's global loads in flight during the MFMAs.
@@ -17,10 +18,21 @@
 namespace galore {
 namespace {
 
-constexpr int BM = 128;
-constexpr int BN = 128;
-constexpr int BK = 32;
 constexpr int NT = 256;
+
+// Workgroup tiles: 128 x 128 x 32 (2 x 2 waves of 64 x 64), or 64 x 64 x 64 (2 x
+// 2 waves of 32 x 32) where a launch has too few of the former to fill the
+// chip. Both take the contraction in the same order, so the results are the
+// same bits.
+template <int TB>
+struct TileShape {
+    static constexpr int BM = TB;
+    static constexpr int BN = TB;
+    static constexpr int BK = TB == 64 ? 64 : 32;
+    // LDS row pitch (odd for the 64-wide tile: the four 16-deep segments a wave
+    // stores side by side fall on distinct banks)
+    static constexpr int LP = TB == 64 ? 65 : 128;
+};
 
 template <typename T>
 __device__ __forceinline__ float load_elem(const T* base, int64_t idx) {
@@ -45,13 +57,15 @@ __device__ __forceinline__ void load_vec16(const bf16_t* src, float* out) {
     }
 }
 
-// A BK x 128 operand tile v(kk, c) = base[(k0 + kk) * ld + c0 + c] whose
+// A BK x TB operand tile v(kk, c) = base[(k0 + kk) * ld + c0 + c] whose
 // second index runs along memory (A stored M-contiguous, B N-contiguous):
 // each thread moves E rows of one 16-byte vector.
-template <typename T>
+template <typename T, int TB>
 struct ContigTile {
+    static constexpr int BK = TileShape<TB>::BK;
+    static constexpr int LP = TileShape<TB>::LP;
     static constexpr int V = 16 / static_cast<int>(sizeof(T));   // elements per vector
-    static constexpr int CQ = 128 / V;                           // vectors per tile row
+    static constexpr int CQ = TB / V;                            // vectors per tile row
     static constexpr int KR = NT / CQ;                           // rows per pass
     static constexpr int E = BK / KR;                            // passes (V * E == 16)
     __device__ static void load(const T* base, int64_t ld, int k0, int K, int c0, int C, bool vec, int t,
@@ -77,7 +91,7 @@ struct ContigTile {
 #pragma unroll
         for (int e = 0; e < E; ++e) load_vec16(src + static_cast<int64_t>(KR * e) * ld, r + V * e);
     }
-    __device__ static void store(float (*S)[128], int t, const float* r) {
+    __device__ static void store(float (*S)[LP], int t, const float* r) {
         const int cq = t % CQ, kr = t / CQ;
 #pragma unroll
         for (int e = 0; e < E; ++e)
@@ -86,16 +100,18 @@ struct ContigTile {
     }
 };
 
-// A BK x 128 operand tile v(kk, c) = base[(c0 + c) * ld + k0 + kk] whose
+// A BK x TB operand tile v(kk, c) = base[(c0 + c) * ld + k0 + kk] whose
 // first (reduction) index runs along memory (A stored K-contiguous, B stored
 // K-contiguous): each thread moves 16 consecutive k of one row.
-template <typename T>
+template <typename T, int TB>
 struct KContigTile {
+    static constexpr int LP = TileShape<TB>::LP;
     static constexpr int V = 16 / static_cast<int>(sizeof(T));
+    static constexpr int SEG = TileShape<TB>::BK / 16;   // threads per row
     __device__ static void load(const T* base, int64_t ld, int k0, int K, int c0, int C, bool vec, int t,
                                 float* r) {
-        const int c = c0 + (t >> 1);
-        const int gk = k0 + (t & 1) * 16;
+        const int c = c0 + t / SEG;
+        const int gk = k0 + (t % SEG) * 16;
         const T* src = base + static_cast<int64_t>(c) * ld + gk;
         if (c < C && gk + 16 <= K && vec) {
 #pragma unroll
@@ -106,24 +122,26 @@ struct KContigTile {
         }
     }
     __device__ static void load_fast(const T* base, int64_t ld, int k0, int c0, int t, float* r) {
-        const T* src = base + static_cast<int64_t>(c0 + (t >> 1)) * ld + k0 + (t & 1) * 16;
+        const T* src = base + static_cast<int64_t>(c0 + t / SEG) * ld + k0 + (t % SEG) * 16;
 #pragma unroll
         for (int q = 0; q < 16 / V; ++q) load_vec16(src + V * q, r + V * q);
     }
-    __device__ static void store(float (*S)[128], int t, const float* r) {
-        const int c = t >> 1;
-        const int kk0 = (t & 1) * 16;
+    __device__ static void store(float (*S)[LP], int t, const float* r) {
+        const int c = t / SEG;
+        const int kk0 = (t % SEG) * 16;
 #pragma unroll
         for (int e = 0; e < 16; ++e) S[kk0 + e][c] = r[e];
     }
 };
 
-template <ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
+template <int TS, ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
 __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, int b_vec) {
+    static_assert(TS == 128 || !PLANES, "the plane epilogue is the 128-wide tile's");
+    constexpr int BM = TileShape<TS>::BM, BN = TileShape<TS>::BN, BK = TileShape<TS>::BK, LP = TileShape<TS>::LP;
     // the two operand stages; the plane epilogue reuses the same 64 KB
-    __shared__ __attribute__((aligned(16))) float smem[2 * BK * BM + 2 * BK * BN];
-    float (*As)[BK][BM] = reinterpret_cast<float (*)[BK][BM]>(smem);
-    float (*Bs)[BK][BN] = reinterpret_cast<float (*)[BK][BN]>(smem + 2 * BK * BM);
+    __shared__ __attribute__((aligned(16))) float smem[4 * BK * LP];
+    float (*As)[BK][LP] = reinterpret_cast<float (*)[BK][LP]>(smem);
+    float (*Bs)[BK][LP] = reinterpret_cast<float (*)[BK][LP]>(smem + 2 * BK * LP);
 
     // XCD-aware, row-grouped tile order (grid = n tiles x m tiles x batch)
     const int num_n = gridDim.x, num_m = gridDim.y;
@@ -151,8 +169,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
     const int wn = wave & 1;
 
     // A tile: rows i of op(A), B tile: columns j of op(B), both BK deep
-    using TileA = typename std::conditional<LA == ALayout::kKContig, KContigTile<TA>, ContigTile<TA>>::type;
-    using TileB = typename std::conditional<LB == BLayout::kKContig, KContigTile<TB>, ContigTile<TB>>::type;
+    using TileA = typename std::conditional<LA == ALayout::kKContig, KContigTile<TA, TS>, ContigTile<TA, TS>>::type;
+    using TileB = typename std::conditional<LB == BLayout::kKContig, KContigTile<TB, TS>, ContigTile<TB, TS>>::type;
 
     float ra[16];
     float rb[16];
@@ -175,10 +193,12 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
     // by all 128 columns: in a tile's last K stages every wave then drops the
     // same column blocks, where the 2 x 2 layout left the waves of the first
     // 64 columns idle at the stage barriers
-    constexpr int WMB = TRIL ? 1 : 2;            // 32-row blocks per wave
-    constexpr int WNB = TRIL ? 4 : 2;            // 32-column blocks per wave
-    const int wr = TRIL ? 32 * wave : 64 * wm;   // the wave's first row in the tile
-    const int wc = TRIL ? 0 : 64 * wn;           // the wave's first column in the tile
+    // (the 64-wide tile: 2 x 2 waves of one block either way)
+    constexpr bool kRows = TRIL && TS == 128;
+    constexpr int WMB = kRows ? 1 : TS / 64;                 // 32-row blocks per wave
+    constexpr int WNB = kRows ? 4 : TS / 64;                 // 32-column blocks per wave
+    const int wr = kRows ? 32 * wave : (TS / 2) * wm;        // the wave's first row in the tile
+    const int wc = kRows ? 0 : (TS / 2) * wn;                // the wave's first column in the tile
     f32x16 acc[WMB][WNB];
 #pragma unroll
     for (int mi = 0; mi < WMB; ++mi)
@@ -246,7 +266,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
                 const int k0 = kt * BK;
                 if (!g.b_upper || k0 < cw + 32) {
                     kstep(cur, std::integral_constant<int, FULL>());
-                } else if constexpr (TRIL) {
+                } else if constexpr (kRows) {
                     // blocks d .. of the wave's four (k0 = cw + 32 d, d = 1 .. 3)
                     const int d = (k0 - cw) >> 5;
                     if (d == 1) {
@@ -256,7 +276,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
                     } else if (d == 3) {
                         if constexpr ((FULL & 0x8) != 0) kstep(cur, std::integral_constant<int, FULL & 0x8>());
                     }
-                } else if (NB > 1 && k0 < cw + 64) {
+                } else if (WNB > 1 && NB > 1 && k0 < cw + 64) {
                     kstep(cur, std::integral_constant<int, (NB > 1) ? 2 : 0>());
                 }
             }
@@ -267,7 +287,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
             __syncthreads();
         }
     };
-    if constexpr (TRIL) {
+    if constexpr (kRows) {
         const int nv = (N - cw + 31) / 32;
         if (nv >= 4) kloop(std::integral_constant<int, 4>());
         else if (nv == 3) kloop(std::integral_constant<int, 3>());
@@ -275,7 +295,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
         else if (nv == 1) kloop(std::integral_constant<int, 1>());
         else kloop(std::integral_constant<int, 0>());
     } else {
-        if (cw + 32 < N) kloop(std::integral_constant<int, 2>());
+        if (WNB > 1 && cw + 32 < N) kloop(std::integral_constant<int, WNB>());
         else if (cw < N) kloop(std::integral_constant<int, 1>());
         else kloop(std::integral_constant<int, 0>());
     }
@@ -345,10 +365,11 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
         return;
     }
 #pragma unroll
-    for (int mi = 0; mi < WMB; ++mi) {
+    for (int ni = 0; ni < WNB; ++ni) {
+        const int c = col0 + wc + ni * 32 + lrow;
+        unsigned mx = 0u;   // bits of the largest |C| of this lane's column
 #pragma unroll
-        for (int ni = 0; ni < WNB; ++ni) {
-            const int c = col0 + wc + ni * 32 + lrow;
+        for (int mi = 0; mi < WMB; ++mi) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int r = row0 + wr + mi * 32 + (v & 3) + 8 * (v >> 2) + 4 * lk;
@@ -357,15 +378,31 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
                     float val = alpha * acc[mi][ni][v];
                     if (beta != 0.0f) val += beta * (*dst);
                     *dst = val;
+                    mx = max(mx, __float_as_uint(fabsf(val)));
                 }
             }
+        }
+        if (g.cmax != nullptr) {
+            // column maxima for the exact Gram of C (non-negative floats order
+            // like their bit patterns; NaN/Inf win), one atomic per column and wave
+            mx = max(mx, static_cast<unsigned>(__shfl_xor(static_cast<int>(mx), 32)));
+            if (lk == 0 && c < N) atomicMax(g.cmax + static_cast<int64_t>(bz) * g.strideCM + c, mx);
         }
     }
 }
 
-template <ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
-hipError_t launch_one(const GemmArgs& g, int batch, hipStream_t stream) {
-    dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, batch);
+// 128-wide tiles up to which a launch takes the 64-wide ones instead: two
+// workgroups of the wide tile share a CU, so up to 512 of them the launch lasts
+// as long as one of them alone, and waits a memory latency per 32-deep stage.
+// The 64-wide tiles bring four times the workgroups and half the stages:
+// A Omega of 16 x 512x1376 (k = 136, 48 wide tiles) 118 -> 74 us, of 6 x
+// 1024x2736 (k = 272, 144) 250 -> 156 us, of one 256x688 (k = 40, 2) 71 -> 26 us;
+// equal at 1056 wide tiles (24 x 2736x1024, r = 256).
+constexpr int64_t kSmallTiles = 512;
+
+template <int TS, ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
+hipError_t launch_tile(const GemmArgs& g, int batch, hipStream_t stream) {
+    dim3 grid((g.N + TS - 1) / TS, (g.M + TS - 1) / TS, batch);
     // 16-byte vector loads need every row start 16-byte aligned
     const int amul = (sizeof(TA) == 4) ? 4 : 8;   // elements per 16-byte vector
     const int bmul = (sizeof(TB) == 4) ? 4 : 8;
@@ -373,8 +410,17 @@ hipError_t launch_one(const GemmArgs& g, int batch, hipStream_t stream) {
                       (reinterpret_cast<uintptr_t>(g.A) % 16 == 0);
     const int b_vec = (g.ldb % bmul == 0) && (batch == 1 || g.strideB % bmul == 0) &&
                       (reinterpret_cast<uintptr_t>(g.B) % 16 == 0);
-    hipLaunchKernelGGL((gemm_f32_kernel<LA, LB, TA, TB, PLANES, TRIL>), grid, dim3(NT), 0, stream, g, a_vec, b_vec);
+    hipLaunchKernelGGL((gemm_f32_kernel<TS, LA, LB, TA, TB, PLANES, TRIL>), grid, dim3(NT), 0, stream, g, a_vec, b_vec);
     return hipGetLastError();
+}
+
+template <ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
+hipError_t launch_one(const GemmArgs& g, int batch, hipStream_t stream) {
+    if constexpr (!PLANES) {
+        const int64_t tiles = static_cast<int64_t>((g.N + 127) / 128) * ((g.M + 127) / 128) * batch;
+        if (tiles <= kSmallTiles) return launch_tile<64, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+    }
+    return launch_tile<128, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
 }
 
 template <ALayout LA, BLayout LB>
@@ -394,7 +440,7 @@ hipError_t launch_gemm(ALayout la, BLayout lb, bool a_bf16, bool b_bf16, const G
         // plane output: fp32 operands, A K-contiguous and B N-contiguous only
         // (the product Y R^-1 of the orthonormalisation)
         if (la != ALayout::kKContig || lb != BLayout::kNContig || a_bf16 || b_bf16 || g.beta != 0.0f ||
-            g.rows_pad < g.M || g.rows_pad > (g.M + BM - 1) / BM * BM || g.ldpl < g.rows_pad ||
+            g.rows_pad < g.M || g.rows_pad > (g.M + 127) / 128 * 128 || g.ldpl < g.rows_pad ||
             g.planeStride < g.ldpl * g.N || (batch > 1 && g.stridePl < 3 * g.planeStride))
             return hipErrorInvalidValue;
         return g.b_upper ? launch_one<ALayout::kKContig, BLayout::kNContig, float, float, true, true>(g, batch, stream)

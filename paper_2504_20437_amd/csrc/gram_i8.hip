@@ -51,46 +51,44 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(unsigned* p, int64_t n) {
 
 // cmax[j] = max over rows of the bits of |x_ij| (non-negative floats order
 // like their bit patterns; NaN and Inf compare above every finite value).
-// Thread t of a workgroup takes column quad t (16-byte row loads, 8 rows in
-// flight) when vec (rows 16-byte aligned, cols a multiple of 4), else single
-// columns; grid (ceil(rows / rb), batch).
+// A workgroup takes rb rows: its threads are dealt out as column quads (single
+// columns where the rows are not 16-byte aligned or cols no multiple of 4) by
+// row groups, a thread walking its group's rows eight at a time; grid
+// (ceil(rows / rb), batch).
+template <int V>
 __global__ __launch_bounds__(256) void colmax_kernel(const float* Xb, int64_t ldx, int64_t strideX, int rows,
-                                                     int cols, int rb, unsigned* cmaxb, int64_t strideCM, int vec) {
+                                                     int cols, int rb, unsigned* cmaxb, int64_t strideCM) {
     const int b = blockIdx.y;
     const float* X = Xb + static_cast<int64_t>(b) * strideX;
     unsigned* cmax = cmaxb + static_cast<int64_t>(b) * strideCM;
     const int i0 = blockIdx.x * rb;
     const int i1 = min(rows, i0 + rb);
-    if (vec) {
-        for (int q = threadIdx.x; 4 * q < cols; q += blockDim.x) {
-            unsigned m[4] = {0u, 0u, 0u, 0u};
-            for (int i = i0; i < i1; i += 8) {
+    const int nq = (cols + V - 1) / V;
+    const int groups = nq >= 256 ? 1 : 256 / nq;   // row groups
+    const int grp = nq >= 256 ? 0 : threadIdx.x / nq;
+    if (grp >= groups) return;
+    for (int q = nq >= 256 ? threadIdx.x : threadIdx.x % nq; q < nq; q += 256) {
+        unsigned m[V];
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (i + e < i1) {
-                        const f32x4 x = *reinterpret_cast<const f32x4*>(X + static_cast<int64_t>(i + e) * ldx + 4 * q);
+        for (int c = 0; c < V; ++c) m[c] = 0u;
+        for (int i = i0 + grp; i < i1; i += 8 * groups) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) m[c] = max(m[c], __float_as_uint(fabsf(x[c])));
+            for (int e = 0; e < 8; ++e) {
+                const int r = i + e * groups;
+                if (r < i1) {
+                    const float* x = X + static_cast<int64_t>(r) * ldx + V * q;
+                    if constexpr (V == 4) {
+                        const f32x4 v = *reinterpret_cast<const f32x4*>(x);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) m[c] = max(m[c], __float_as_uint(fabsf(v[c])));
+                    } else {
+                        m[0] = max(m[0], __float_as_uint(fabsf(x[0])));
                     }
+                }
             }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) atomicMax(cmax + 4 * q + c, m[c]);
-        }
-        return;
-    }
-    for (int j = threadIdx.x; j < cols; j += blockDim.x) {
-        unsigned m[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) m[e] = 0u;
-        // 16 independent loads in flight per thread
-        for (int i = i0; i < i1; i += 16) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (i + e < i1) m[e] = max(m[e], __float_as_uint(fabsf(X[static_cast<int64_t>(i + e) * ldx + j])));
         }
 #pragma unroll
-        for (int e = 1; e < 16; ++e) m[0] = max(m[0], m[e]);
-        atomicMax(cmax + j, m[0]);
+        for (int c = 0; c < V; ++c) atomicMax(cmax + V * q + c, m[c]);
     }
 }
 
@@ -365,12 +363,20 @@ hipError_t launch_gram_i8(const GramI8Args& g, int batch, hipStream_t stream) {
     if (!g.cmax_ready) {
         const hipError_t e = launch_fill_u32(g.cmax, g.strideCM * batch, stream);
         if (e != hipSuccess) return e;
-        const int rb = 128;
-        dim3 grid((g.rows + rb - 1) / rb, batch);
+        // 128 rows a workgroup, fewer (a pass of eight loads a thread) where that
+        // leaves the chip idle (16 x 512 rows of 136 columns: 37 -> 10 us)
         const int vec = (g.cols % 4 == 0) && (g.ldx % 4 == 0) && (batch == 1 || g.strideX % 4 == 0) &&
                         (reinterpret_cast<uintptr_t>(g.X) % 16 == 0);
-        hipLaunchKernelGGL(colmax_kernel, grid, dim3(256), 0, stream, g.X, g.ldx, g.strideX, g.rows, g.cols, rb,
-                           g.cmax, g.strideCM, vec);
+        const int nq = vec ? g.cols / 4 : g.cols;
+        int rb = 8 * (nq >= 256 ? 1 : 256 / nq);
+        while (rb < 128 && static_cast<int64_t>(g.rows) * batch > static_cast<int64_t>(rb) * 1024) rb *= 2;
+        dim3 grid((g.rows + rb - 1) / rb, batch);
+        if (vec)
+            hipLaunchKernelGGL(colmax_kernel<4>, grid, dim3(256), 0, stream, g.X, g.ldx, g.strideX, g.rows, g.cols, rb,
+                               g.cmax, g.strideCM);
+        else
+            hipLaunchKernelGGL(colmax_kernel<1>, grid, dim3(256), 0, stream, g.X, g.ldx, g.strideX, g.rows, g.cols, rb,
+                               g.cmax, g.strideCM);
     }
     {
         // 16-byte row loads where every row start of X is aligned (the digit
