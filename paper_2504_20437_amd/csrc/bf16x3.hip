@@ -214,7 +214,6 @@ struct Bx3Args {
 // fall on distinct banks of the 64-bank LDS. Rows past M (or N) load row
 // M - 1 (N - 1) instead and are never stored.
 // --------------------------------------------------------------------------
-constexpr int YM = 256;
 constexpr int YN = 128;
 constexpr int YT = 256;
 // tile order (measured on 64 x 4096x11008: XCD-contiguous ids 55 ms per
@@ -254,13 +253,15 @@ __device__ __forceinline__ void wait_stages(int ahead) {
 // PA = 3: both operands hold three planes (fp32 x fp32): the six products
 // A_i B_j with i + j <= 4 (planes counted from 1); the three left out are below
 // 2^-26 of |A||B| in size, under fp32 rounding.
-template <int YK, int S, bool AT, int PA, int PB = 3, int WN = 2>
-__global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <= 81920) ? 2 : 1) void gemm_bf16x3_direct_kernel(Bx3Args g) {
+// MB: 32-row blocks per wave (tile of 64 MB rows).
+template <int YK, int S, bool AT, int PA, int PB = 3, int WN = 2, int MB = 4>
+__global__ __launch_bounds__(128 * WN, (S * (PA * 64 * MB + PB * 64 * WN) * YK * 2 <= 81920) ? 2 : 1) void gemm_bf16x3_direct_kernel(Bx3Args g) {
     static_assert(!AT || YK == 32, "the M-contiguous A stage assumes 32-deep stages");
     static_assert(PA == 1 || (PA == 3 && !AT), "three A planes are K-contiguous");
     static_assert(PB == 3 || (PB == 1 && PA == 1), "one B plane pairs with one A plane");
     static_assert(WN == 2 || (WN == 4 && !AT), "four waves across N: K-contiguous A only");
-    // WN waves across the tile's columns (64 each), two down its rows (128 each)
+    // WN waves across the tile's columns (64 each), two down its rows (32 MB each)
+    constexpr int YM = 64 * MB;
     constexpr int YN = 64 * WN;
     constexpr int YT = 128 * WN;
     // the stage's two steps read and multiplied in order, the next stage's
@@ -310,11 +311,12 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
     for (int i = 0; i < LA; ++i) {
         const int j = wave * LA + i;
         if constexpr (AT) {
-            // M-contiguous A (A[kk * lda + i]): a stage row is one kk, 256 m
-            // (32 chunks, 512 bytes), chunk c at slot c ^ (4 (kk % 4)); a direct
-            // load fills 2 rows; chunks past the row load its last one
-            const int sr = 2 * j + (lane >> 5);
-            const int slot = lane & 31;
+            // M-contiguous A (A[kk * lda + i]): a stage row is one kk, YM m (YM / 8
+            // chunks), chunk c at slot c ^ (4 (kk % 4)); chunks past the row load
+            // its last one
+            constexpr int CPM = YM / 8;
+            const int sr = (64 / CPM) * j + lane / CPM;
+            const int slot = lane % CPM;
             const int m = min(row0 + 8 * (slot ^ (4 * (sr & 3))), g.mload - 8);
             srcA[i] = A + static_cast<int64_t>(sr) * g.lda + m;
         } else {
@@ -344,9 +346,9 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
         for (int i = 0; i < LB; ++i) load_lds16(srcB[i] + k0, base + kStageA + (wave * LB + i) * 1024);
     };
 
-    f32x16 acc[4][2];
+    f32x16 acc[MB][2];
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < MB; ++x)
 #pragma unroll
         for (int y = 0; y < 2; ++y)
 #pragma unroll
@@ -370,23 +372,23 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
         const unsigned char* sa = ysm + (kt % S) * kStage;
         const unsigned char* sb = sa + kStageA;
         // fragments of 16-deep step ks into register buffer fb
-        bf16x8 a[kFragBufs][PA][4], bq[kFragBufs][PB][2];
+        bf16x8 a[kFragBufs][PA][MB], bq[kFragBufs][PB][2];
         auto fetch = [&](int fb, int ks) {
             const int c = 2 * ks + lk;
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
+            for (int x = 0; x < MB; ++x) {
                 if constexpr (AT) {
                     // transposing LDS reads: in each group of 16 lanes, lane j
                     // receives element j % 4 of lanes 4 e + j / 4 (e = 0..3). Lane
                     // L of the group points at row kk = kb + L / 4, m = mb + 4 (L % 4),
                     // so lane j gets A[mb + j][kb .. kb + 3]
                     const int L = lane & 15;
-                    const int m = wm * 128 + 32 * x + 16 * ((lane >> 4) & 1) + 4 * (L & 3);
+                    const int m = wm * (32 * MB) + 32 * x + 16 * ((lane >> 4) & 1) + 4 * (L & 3);
                     bf16x4 h2[2];
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int kk = 16 * ks + 8 * lk + 4 * h + (L >> 2);
-                        const int off = kk * 512 + 16 * ((m >> 3) ^ (4 * (kk & 3))) + 2 * (m & 7);
+                        const int off = kk * (2 * YM) + 16 * ((m >> 3) ^ (4 * (kk & 3))) + 2 * (m & 7);
                         h2[h] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
                             reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(
                                 reinterpret_cast<__attribute__((address_space(3))) unsigned char*>(
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                     }
                     a[fb][0][x] = __builtin_shufflevector(h2[0], h2[1], 0, 1, 2, 3, 4, 5, 6, 7);
                 } else {
-                    const int r = wm * 128 + 32 * x + l32;
+                    const int r = wm * (32 * MB) + 32 * x + l32;
 #pragma unroll
                     for (int pa = 0; pa < PA; ++pa)
                         a[fb][pa][x] = *reinterpret_cast<const bf16x8*>(sa + pa * (YM * RB) + r * RB +
@@ -415,7 +417,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
 #pragma unroll
                 for (int p = 0; p < PB; ++p)
 #pragma unroll
-                    for (int x = 0; x < 4; ++x)
+                    for (int x = 0; x < MB; ++x)
 #pragma unroll
                         for (int y = 0; y < NB; ++y)
                             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[fb][0][x], bq[fb][p][y], acc[x][y],
@@ -425,7 +427,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
 #pragma unroll
                 for (int q = 0; q < 6; ++q)
 #pragma unroll
-                    for (int x = 0; x < 4; ++x)
+                    for (int x = 0; x < MB; ++x)
 #pragma unroll
                         for (int y = 0; y < NB; ++y)
                             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -505,7 +507,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
             // one n, i.e. four consecutive entries of row n of the stored matrix
             const bool v4 = (g.ldc % 4) == 0 && (reinterpret_cast<uintptr_t>(C) % 16) == 0;
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
+            for (int x = 0; x < MB; ++x) {
 #pragma unroll
                 for (int y = 0; y < 2; ++y) {
                     const int c = col0 + wn * 64 + 32 * y + l32;
@@ -519,7 +521,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                     if (beta != 0.0f) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            const int r = row0 + wm * 128 + 32 * x + 8 * q + 4 * lk;
+                            const int r = row0 + wm * (32 * MB) + 32 * x + 8 * q + 4 * lk;
                             const float* src = C + static_cast<int64_t>(c) * g.ldc;
                             if (v4 && (full_tile || r + 4 <= M)) {
                                 old[q] = *reinterpret_cast<const f32x4*>(src + r);
@@ -531,7 +533,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                     }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const int r = row0 + wm * 128 + 32 * x + 8 * q + 4 * lk;
+                        const int r = row0 + wm * (32 * MB) + 32 * x + 8 * q + 4 * lk;
                         float* dst = C + static_cast<int64_t>(c) * g.ldc + r;
                         f32x4 val = {al * acc[x][y][4 * q], al * acc[x][y][4 * q + 1], al * acc[x][y][4 * q + 2],
                                      al * acc[x][y][4 * q + 3]};
@@ -552,7 +554,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
             return;
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < MB; ++x) {
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const int c = col0 + wn * 64 + 32 * y + l32;
@@ -565,7 +567,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                     const int cc = min(c, N - 1);
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int r = row0 + wm * 128 + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
+                        const int r = row0 + wm * (32 * MB) + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
                         old[v] = C[static_cast<int64_t>(min(r, M - 1)) * g.ldc + cc];
                     }
                 }
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                     // would wait again for the reads above before every store
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int r = row0 + wm * 128 + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
+                        const int r = row0 + wm * (32 * MB) + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
                         float val = al * acc[x][y][v];
                         if (beta != 0.0f) val += beta * old[v];
                         C[static_cast<int64_t>(r) * g.ldc + c] = val;
@@ -583,7 +585,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                 } else {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int r = row0 + wm * 128 + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
+                        const int r = row0 + wm * (32 * MB) + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
                         if (r < M && c < N) {
                             float* dst = C + static_cast<int64_t>(r) * g.ldc + c;
                             float val = al * acc[x][y][v];
@@ -601,7 +603,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
             // one n, i.e. four consecutive entries of row n of the stored matrix
             const bool v4 = (g.ldc % 4) == 0 && (reinterpret_cast<uintptr_t>(C) % 16) == 0;
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
+            for (int x = 0; x < MB; ++x) {
 #pragma unroll
                 for (int y = 0; y < 2; ++y) {
                     const int c = col0 + wn * 64 + 32 * y + l32;
@@ -609,7 +611,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
                     const float al = g.nscale ? alpha * g.nscale[static_cast<int64_t>(bz) * g.strideNS + c] : alpha;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const int r = row0 + wm * 128 + 32 * x + 8 * q + 4 * lk;
+                        const int r = row0 + wm * (32 * MB) + 32 * x + 8 * q + 4 * lk;
                         float* dst = C + static_cast<int64_t>(c) * g.ldc + r;
                         f32x4 val = {al * acc[x][y][4 * q], al * acc[x][y][4 * q + 1], al * acc[x][y][4 * q + 2],
                                      al * acc[x][y][4 * q + 3]};
@@ -631,14 +633,14 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * YM + PB * 64 * WN) * YK * 2 <=
             return;
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < MB; ++x) {
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
                 const int c = col0 + wn * 64 + 32 * y + l32;
                 const float al = (g.nscale && c < N) ? alpha * g.nscale[static_cast<int64_t>(bz) * g.strideNS + c] : alpha;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int r = row0 + wm * 128 + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
+                    const int r = row0 + wm * (32 * MB) + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
                     if (r < M && c < N) {
                         float* dst = C + static_cast<int64_t>(r) * g.ldc + c;
                         float val = al * acc[x][y][v];
@@ -695,6 +697,27 @@ constexpr int kDirectST = GALORE_BX3T_S;   // stages of the M-contiguous-A kerne
 constexpr int kX6K = GALORE_BX6_K;         // K depth of a stage
 constexpr int kX6S = GALORE_BX6_S;         // stages in LDS
 constexpr int kX6WN = GALORE_BX6_WN;       // waves across N (tile 256 x 64 WN)
+
+// 128-row tiles instead of 256-row ones where the latter leave CUs idle. One
+// 4096x11008 matrix (144 wide tiles): the sketch product 246 -> 191 us, A X 467
+// -> 439 us; with every CU taken the half tiles lose, staging B twice as often
+// (344 wide tiles, the projection of one 11008x4096: 332 against 372 us).
+bool half_tiles(int M, int N, int tile_n, int batch) {
+    return static_cast<int64_t>((N + tile_n - 1) / tile_n) * ((M + 255) / 256) * batch <= 256;
+}
+
+// The six-plane product on 128 x 128 tiles, two workgroups per CU, instead of 256
+// x 256, one per CU: whole rounds of tiles over the chip, the smaller ones at
+// 1.3 times the cost for the same work (11008x4096, r = 1024, 688 wide tiles: 640
+// against 839 us). They win where the wide tiles fill the chip badly: one
+// 512x1376, r = 128 (12 wide tiles) 36 -> 17 us, a 4096 x 1024 projector (64) 147
+// -> 76 us, 6 x 1024x2736, r = 256 (264, one past a round) 120 -> 95 us; not at
+// 1056 (24 x 2736x1024, 343 against 360 us).
+bool six_plane_small(int M, int N, int batch) {
+    const int64_t wide = static_cast<int64_t>((N + 255) / 256) * ((M + 255) / 256) * batch;
+    const int64_t small = static_cast<int64_t>((N + 127) / 128) * ((M + 127) / 128) * batch;
+    return 13 * ((small + 511) / 512) < 20 * ((wide + 255) / 256);
+}
 
 }  // namespace
 
@@ -772,21 +795,24 @@ hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a
     if (!bf16x3_direct_ok(A, lda, strideA, Bplanes, ldb, planeStride, strideB, g.mload, K, batch, a_mcontig) ||
         (a_mcontig && g.mload < M))
         return hipErrorInvalidValue;
-    {
-        dim3 grid((N + YN - 1) / YN, (M + YM - 1) / YM, batch);
-        if (planesB == 1) {
-            if (a_mcontig)
-                hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<32, kDirectST, true, 1, 1>), grid, dim3(YT), 0, stream, g);
-            else
-                hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1, 1>), grid, dim3(YT), 0,
-                                   stream, g);
-        } else if (a_mcontig) {
-            hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<32, kDirectST, true, 1>), grid, dim3(YT), 0, stream, g);
-        } else {
-            hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1>), grid, dim3(YT), 0, stream, g);
-        }
+    const bool half = half_tiles(M, N, YN, batch);
+    auto run = [&](auto kernel, int tile_m) {
+        dim3 grid((N + YN - 1) / YN, (M + tile_m - 1) / tile_m, batch);
+        hipLaunchKernelGGL(kernel, grid, dim3(YT), 0, stream, g);
         return hipGetLastError();
+    };
+    if (planesB == 1) {
+        if (a_mcontig)
+            return half ? run(gemm_bf16x3_direct_kernel<32, kDirectST, true, 1, 1, 2, 2>, 128)
+                        : run(gemm_bf16x3_direct_kernel<32, kDirectST, true, 1, 1>, 256);
+        return half ? run(gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1, 1, 2, 2>, 128)
+                    : run(gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1, 1>, 256);
     }
+    if (a_mcontig)
+        return half ? run(gemm_bf16x3_direct_kernel<32, kDirectST, true, 1, 3, 2, 2>, 128)
+                    : run(gemm_bf16x3_direct_kernel<32, kDirectST, true, 1>, 256);
+    return half ? run(gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1, 3, 2, 2>, 128)
+                : run(gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1>, 256);
 }
 
 hipError_t launch_split3_rows(const float* src, int64_t lds, int64_t strideS, void* planes, int64_t ldp,
@@ -839,7 +865,12 @@ hipError_t launch_gemm_bf16x6(const void* Aplanes, int64_t lda, int64_t planeStr
     g.b_upper = b_upper;
     g.cmax = nullptr;
     g.strideCM = 0;
-    dim3 grid((N + 64 * kX6WN - 1) / (64 * kX6WN), (M + YM - 1) / YM, batch);
+    if (six_plane_small(M, N, batch)) {
+        dim3 grid((N + 127) / 128, (M + 127) / 128, batch);
+        hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<kX6K, kX6S, false, 3, 3, 2, 2>), grid, dim3(256), 0, stream, g);
+        return hipGetLastError();
+    }
+    dim3 grid((N + 64 * kX6WN - 1) / (64 * kX6WN), (M + 255) / 256, batch);
     hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<kX6K, kX6S, false, 3, 3, kX6WN>), grid, dim3(128 * kX6WN), 0, stream,
                        g);
     return hipGetLastError();

@@ -1132,3 +1132,32 @@ def test_fp32_products_tile_forms_agree(gl, m, n, r):
     D = P64 @ N64 if m <= n else (P64 @ N64).T
     Db = np.abs(P64) @ np.abs(N64)
     assert np.all(np.abs(host(W1)[0] + D) <= (r + 4) * 2.0 ** -24 * (Db if m <= n else Db.T))
+
+
+@pytest.mark.parametrize("m,n,r", [(128, 136, 32), (136, 128, 64), (264, 160, 96), (160, 520, 32)])
+def test_bf16_products_tile_forms_agree(gl, m, n, r):
+    """The bf16 plane products take half-height tiles (three planes) and 128-wide
+    tiles (six planes) where a launch has few tiles: the same bits as the wide
+    ones, which a large batch takes (projection, low-bit projection,
+    back-projection and update, both orientations, at and beside the tiles)."""
+    import torch
+    s, l = min(m, n), max(m, n)
+    rng = np.random.default_rng(m * n)
+    batch = 600
+    G = torch.from_numpy(rng.standard_normal((m, n)).astype(np.float32)).cuda().to(torch.bfloat16)
+    P = dev(np.linalg.qr(rng.standard_normal((s, r)))[0].astype(np.float32))
+    N = dev(rng.standard_normal((r, l)).astype(np.float32))
+    Gb, Pb, Nb = (x.expand(batch, *x.shape).contiguous() for x in (G, P, N))
+    out = []
+    for b in (1, batch):
+        W = torch.zeros((b, m, n), device="cuda")
+        R = gl.galore_project(Pb[:b], Gb[:b])
+        gl.galore_project_back(Pb[:b], Nb[:b], W, 1.0, 1.0)
+        Rq = gl.galore_project_quantized(gl.galore_quantize_projector(Pb[:b]), Gb[:b])
+        Pn, sig, info = gl.galore_rsvd_update(Gb[:b], r, 0, 1, 7)
+        assert int(info.max().cpu()) == 0
+        out.append((R, W, Rq, Pn, sig))
+    for one, many in zip(*out):
+        assert torch.equal(one[0], many[0])
+    for many in out[1][:3]:
+        assert torch.equal(many[0], many[batch - 1])
