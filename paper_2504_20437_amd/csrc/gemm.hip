@@ -20,18 +20,21 @@ namespace {
 
 constexpr int NT = 256;
 
-// Workgroup tiles: 128 x 128 x 32 (2 x 2 waves of 64 x 64), or 64 x 64 x 64 (2 x
-// 2 waves of 32 x 32) where a launch has too few of the former to fill the
-// chip. Both take the contraction in the same order, so the results are the
-// same bits.
-template <int TB>
+// Workgroup tiles: 128 x 128 x 32 (2 x 2 waves of 64 x 64, two workgroups per
+// CU), 64 x 64 x 64 (2 x 2 waves of 32 x 32, two per CU) where a launch has too
+// few of the former to fill the chip, and 64 x 64 x 32 (four per CU). All take
+// the contraction in the same order, so the results are the same bits.
+enum Tile { kTile128, kTile64, kTile64x4 };
+template <int TS>
 struct TileShape {
-    static constexpr int BM = TB;
-    static constexpr int BN = TB;
-    static constexpr int BK = TB == 64 ? 64 : 32;
-    // LDS row pitch (odd for the 64-wide tile: the four 16-deep segments a wave
-    // stores side by side fall on distinct banks)
-    static constexpr int LP = TB == 64 ? 65 : 128;
+    static constexpr int BM = TS == kTile128 ? 128 : 64;
+    static constexpr int BN = BM;
+    static constexpr int BK = TS == kTile64 ? 64 : 32;
+    // LDS row pitch (odd for the 64-wide tiles: the segments a wave stores side
+    // by side fall on distinct banks)
+    static constexpr int LP = TS == kTile128 ? 128 : 65;
+    static constexpr int E = BM * BK / NT;              // elements of a tile per thread
+    static constexpr int PER_CU = TS == kTile64x4 ? 4 : 2;
 };
 
 template <typename T>
@@ -57,17 +60,17 @@ __device__ __forceinline__ void load_vec16(const bf16_t* src, float* out) {
     }
 }
 
-// A BK x TB operand tile v(kk, c) = base[(k0 + kk) * ld + c0 + c] whose
+// A BK x BM operand tile v(kk, c) = base[(k0 + kk) * ld + c0 + c] whose
 // second index runs along memory (A stored M-contiguous, B N-contiguous):
 // each thread moves E rows of one 16-byte vector.
-template <typename T, int TB>
+template <typename T, int TS>
 struct ContigTile {
-    static constexpr int BK = TileShape<TB>::BK;
-    static constexpr int LP = TileShape<TB>::LP;
+    static constexpr int BK = TileShape<TS>::BK;
+    static constexpr int LP = TileShape<TS>::LP;
     static constexpr int V = 16 / static_cast<int>(sizeof(T));   // elements per vector
-    static constexpr int CQ = TB / V;                            // vectors per tile row
+    static constexpr int CQ = TileShape<TS>::BM / V;             // vectors per tile row
     static constexpr int KR = NT / CQ;                           // rows per pass
-    static constexpr int E = BK / KR;                            // passes (V * E == 16)
+    static constexpr int E = BK / KR;                            // passes
     __device__ static void load(const T* base, int64_t ld, int k0, int K, int c0, int C, bool vec, int t,
                                 float* r) {
         const int cq = t % CQ, kr = t / CQ;
@@ -100,43 +103,44 @@ struct ContigTile {
     }
 };
 
-// A BK x TB operand tile v(kk, c) = base[(c0 + c) * ld + k0 + kk] whose
+// A BK x BM operand tile v(kk, c) = base[(c0 + c) * ld + k0 + kk] whose
 // first (reduction) index runs along memory (A stored K-contiguous, B stored
-// K-contiguous): each thread moves 16 consecutive k of one row.
-template <typename T, int TB>
+// K-contiguous): each thread moves E consecutive k of one row.
+template <typename T, int TS>
 struct KContigTile {
-    static constexpr int LP = TileShape<TB>::LP;
+    static constexpr int LP = TileShape<TS>::LP;
+    static constexpr int E = TileShape<TS>::E;           // consecutive k per thread
     static constexpr int V = 16 / static_cast<int>(sizeof(T));
-    static constexpr int SEG = TileShape<TB>::BK / 16;   // threads per row
+    static constexpr int SEG = TileShape<TS>::BK / E;    // threads per row
     __device__ static void load(const T* base, int64_t ld, int k0, int K, int c0, int C, bool vec, int t,
                                 float* r) {
         const int c = c0 + t / SEG;
-        const int gk = k0 + (t % SEG) * 16;
+        const int gk = k0 + (t % SEG) * E;
         const T* src = base + static_cast<int64_t>(c) * ld + gk;
-        if (c < C && gk + 16 <= K && vec) {
+        if (c < C && gk + E <= K && vec) {
 #pragma unroll
-            for (int q = 0; q < 16 / V; ++q) load_vec16(src + V * q, r + V * q);
+            for (int q = 0; q < E / V; ++q) load_vec16(src + V * q, r + V * q);
         } else {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) r[e] = (c < C && gk + e < K) ? to_f32(src[e]) : 0.0f;
+            for (int e = 0; e < E; ++e) r[e] = (c < C && gk + e < K) ? to_f32(src[e]) : 0.0f;
         }
     }
     __device__ static void load_fast(const T* base, int64_t ld, int k0, int c0, int t, float* r) {
-        const T* src = base + static_cast<int64_t>(c0 + t / SEG) * ld + k0 + (t % SEG) * 16;
+        const T* src = base + static_cast<int64_t>(c0 + t / SEG) * ld + k0 + (t % SEG) * E;
 #pragma unroll
-        for (int q = 0; q < 16 / V; ++q) load_vec16(src + V * q, r + V * q);
+        for (int q = 0; q < E / V; ++q) load_vec16(src + V * q, r + V * q);
     }
     __device__ static void store(float (*S)[LP], int t, const float* r) {
         const int c = t / SEG;
-        const int kk0 = (t % SEG) * 16;
+        const int kk0 = (t % SEG) * E;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) S[kk0 + e][c] = r[e];
+        for (int e = 0; e < E; ++e) S[kk0 + e][c] = r[e];
     }
 };
 
 template <int TS, ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
-__global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, int b_vec) {
-    static_assert(TS == 128 || !PLANES, "the plane epilogue is the 128-wide tile's");
+__global__ __launch_bounds__(NT, TileShape<TS>::PER_CU) void gemm_f32_kernel(GemmArgs g, int a_vec, int b_vec) {
+    static_assert(TS == kTile128 || !PLANES, "the plane epilogue is the 128-wide tile's");
     constexpr int BM = TileShape<TS>::BM, BN = TileShape<TS>::BN, BK = TileShape<TS>::BK, LP = TileShape<TS>::LP;
     // the two operand stages; the plane epilogue reuses the same 64 KB
     __shared__ __attribute__((aligned(16))) float smem[4 * BK * LP];
@@ -172,8 +176,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
     using TileA = typename std::conditional<LA == ALayout::kKContig, KContigTile<TA, TS>, ContigTile<TA, TS>>::type;
     using TileB = typename std::conditional<LB == BLayout::kKContig, KContigTile<TB, TS>, ContigTile<TB, TS>>::type;
 
-    float ra[16];
-    float rb[16];
+    float ra[TileShape<TS>::E];
+    float rb[TileShape<TS>::E];
     // interior tiles (uniform per workgroup) take the unconditional vector path
     const bool a_full = a_vec && row0 + BM <= M;
     const bool b_full = b_vec && col0 + BN <= N;
@@ -194,11 +198,11 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
     // same column blocks, where the 2 x 2 layout left the waves of the first
     // 64 columns idle at the stage barriers
     // (the 64-wide tile: 2 x 2 waves of one block either way)
-    constexpr bool kRows = TRIL && TS == 128;
-    constexpr int WMB = kRows ? 1 : TS / 64;                 // 32-row blocks per wave
-    constexpr int WNB = kRows ? 4 : TS / 64;                 // 32-column blocks per wave
-    const int wr = kRows ? 32 * wave : (TS / 2) * wm;        // the wave's first row in the tile
-    const int wc = kRows ? 0 : (TS / 2) * wn;                // the wave's first column in the tile
+    constexpr bool kRows = TRIL && TS == kTile128;
+    constexpr int WMB = kRows ? 1 : BM / 64;                 // 32-row blocks per wave
+    constexpr int WNB = kRows ? 4 : BN / 64;                 // 32-column blocks per wave
+    const int wr = kRows ? 32 * wave : (BM / 2) * wm;        // the wave's first row in the tile
+    const int wc = kRows ? 0 : (BN / 2) * wn;                // the wave's first column in the tile
     f32x16 acc[WMB][WNB];
 #pragma unroll
     for (int mi = 0; mi < WMB; ++mi)
@@ -399,10 +403,17 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(GemmArgs g, int a_vec, 
 // 1024x2736 (k = 272, 144) 250 -> 156 us, of one 256x688 (k = 40, 2) 71 -> 26 us;
 // equal at 1056 wide tiles (24 x 2736x1024, r = 256).
 constexpr int64_t kSmallTiles = 512;
+// and up to which it takes 64-wide tiles of half the depth, four to a CU: the
+// wide ones' last round, of 512, is then mostly empty (projections of 24 x
+// 2736x1024, r = 256, 1056 wide tiles: 442 -> 415 us; of 16 x 3000x1500, r = 300,
+// 1152: 566 -> 460 us; of 2 x 4096x11008, r = 1024, 1376: 1779 -> 1840 us, of 2 x
+// 11008x4096 equal). The triangular product keeps the wide tile's 4 x 1 waves.
+constexpr int64_t kMidTiles = 1280;
 
 template <int TS, ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
 hipError_t launch_tile(const GemmArgs& g, int batch, hipStream_t stream) {
-    dim3 grid((g.N + TS - 1) / TS, (g.M + TS - 1) / TS, batch);
+    constexpr int T = TileShape<TS>::BM;
+    dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T, batch);
     // 16-byte vector loads need every row start 16-byte aligned
     const int amul = (sizeof(TA) == 4) ? 4 : 8;   // elements per 16-byte vector
     const int bmul = (sizeof(TB) == 4) ? 4 : 8;
@@ -418,9 +429,12 @@ template <ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false,
 hipError_t launch_one(const GemmArgs& g, int batch, hipStream_t stream) {
     if constexpr (!PLANES) {
         const int64_t tiles = static_cast<int64_t>((g.N + 127) / 128) * ((g.M + 127) / 128) * batch;
-        if (tiles <= kSmallTiles) return launch_tile<64, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+        if (tiles <= kSmallTiles) return launch_tile<kTile64, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+        if constexpr (!TRIL) {
+            if (tiles <= kMidTiles) return launch_tile<kTile64x4, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+        }
     }
-    return launch_tile<128, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+    return launch_tile<kTile128, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
 }
 
 template <ALayout LA, BLayout LB>
