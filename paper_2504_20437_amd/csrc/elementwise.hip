@@ -15,17 +15,22 @@
 namespace galore {
 namespace {
 
-constexpr int SF_COLS = 64;
-constexpr int SF_GROUPS = 4;
+// sign_fix and align take 16 columns (64 bytes of a row) a workgroup of 512
+// threads: the scan down the rows waits a memory latency per few rows, so it is
+// split over many threads and the columns over many workgroups (64 columns and
+// 256 threads left one 4096 x 1024 projector to 16 workgroups: 88 us and 209 us;
+// now 32 us and 61 us).
+constexpr int SF_COLS = 16;
+constexpr int SF_GROUPS = 32;
 
-// A workgroup owns 64 columns of one matrix: thread t scans column quad
-// t & 15 (four columns, one 16-byte load per row when the rows are aligned) over
-// the rows t >> 4, t >> 4 + 16, ... in increasing order, four rows in flight;
-// the 16 row groups are reduced through LDS (larger magnitude, then lower
-// row), and the columns whose chosen entry is negative are negated in a
-// second pass with the same access pattern.
-constexpr int SF_QUADS = SF_COLS / 4;                 // 16 column quads
-constexpr int SF_RGROUPS = SF_COLS * SF_GROUPS / SF_QUADS;   // 16 row groups
+// A workgroup owns SF_COLS columns of one matrix: thread t scans column quad
+// t % SF_QUADS (four columns, one 16-byte load per row when the rows are
+// aligned) over the rows t / SF_QUADS, + SF_RGROUPS, ... in increasing order,
+// four rows in flight; the row groups are reduced through LDS (larger magnitude,
+// then lower row), and the columns whose chosen entry is negative are negated in
+// a second pass with the same access pattern.
+constexpr int SF_QUADS = SF_COLS / 4;
+constexpr int SF_RGROUPS = SF_COLS * SF_GROUPS / SF_QUADS;
 
 __global__ __launch_bounds__(SF_COLS* SF_GROUPS) void sign_fix_kernel(float* Pb, int rows, int r,
                                                                       int64_t ldp, int64_t strideP, int vec) {
@@ -111,7 +116,7 @@ __global__ __launch_bounds__(SF_COLS* SF_GROUPS) void sign_fix_kernel(float* Pb,
     }
 }
 
-// Subspace switch: a workgroup owns 64 columns of one matrix (4 row groups);
+// Subspace switch: a workgroup owns SF_COLS columns of one matrix (SF_GROUPS row groups);
 // the overlap <p_old_j, p_new_j> is summed in fp64 from the exact fp32
 // products, and column j of the new projector is negated in place when it is
 // negative (zero or NaN keeps the sign; paper §4.1.3 sign indeterminacy).

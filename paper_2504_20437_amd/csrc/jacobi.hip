@@ -1005,10 +1005,10 @@ __global__ __launch_bounds__(256) void jacobi_norms_kernel(const float* Ytb, int
 // the blocks of a norm-ordered matrix pairs columns of like size first and
 // cuts the rotations the later sweeps need (about 17% fewer pair rotations
 // and one sweep fewer on the 4096 x 11008 workload in a CPU model of these
-// sweeps). The rank of column c is the number of columns ahead of it; one
-// thread per column, (k / 256) workgroups per matrix, each with the matrix's
-// norms in LDS (one workgroup of 1024 threads per matrix took 63-124 us a
-// sweep); converged matrices are skipped.
+// sweeps). The rank of column c is the number of columns ahead of it, counted by
+// eight threads a column, 32 columns a workgroup, each with the matrix's norms
+// in LDS (k = 1056: 8 us; one thread a column took 36 us, one workgroup of
+// 1024 threads per matrix 63-124 us a sweep); converged matrices are skipped.
 __global__ __launch_bounds__(256) void jacobi_order_kernel(const double* normsb, int k, int* jpermb,
                                                            const int* rotb, int max_sweeps, int sweep) {
     const int b = blockIdx.y;
@@ -1020,15 +1020,16 @@ __global__ __launch_bounds__(256) void jacobi_order_kernel(const double* normsb,
         nv[c] = (v == v) ? v : -1.0;
     }
     __syncthreads();
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= k) return;
-    const double vc = nv[c];
+    const int c = 32 * blockIdx.x + (threadIdx.x >> 3);
+    const double vc = nv[min(c, k - 1)];
     int rank = 0;
-    for (int c2 = 0; c2 < k; ++c2) {
+#pragma unroll 4
+    for (int c2 = threadIdx.x & 7; c2 < k; c2 += 8) {
         const double v2 = nv[c2];
         rank += (v2 > vc) || (v2 == vc && c2 < c);
     }
-    jpermb[static_cast<int64_t>(b) * k + rank] = c;
+    for (int o = 4; o > 0; o >>= 1) rank += __shfl_xor(rank, o);
+    if ((threadIdx.x & 7) == 0 && c < k) jpermb[static_cast<int64_t>(b) * k + rank] = c;
 }
 
 // Xa[j][:] = y_perm(j) / sigma_perm(j) (row j of the result contiguous) for the
@@ -1072,12 +1073,14 @@ __global__ __launch_bounds__(256) void jacobi_finalize_kernel(const float* Ytb, 
         sig[c] = normsb[static_cast<int64_t>(b) * k + c];
         perm[c] = permb[static_cast<int64_t>(b) * k + c];
     }
+    if (tid == 0) nkeep_s = r;
     __syncthreads();
-    if (tid == 0) {
-        int nk = 0;
-        while (nk < r && sig[perm[nk]] > 0.0) ++nk;      // NaN and zero columns end the run
-        nkeep_s = nk;
-    }
+    // kept columns: up to the first that is zero or NaN
+    for (int j = tid; j < r; j += blockDim.x)
+        if (!(sig[perm[j]] > 0.0)) {
+            atomicMin(&nkeep_s, j);
+            break;
+        }
     if (sigma != nullptr) {
         for (int j = tid; j < r; j += blockDim.x) {
             const double v = ldexp(sig[perm[j]], -expb[b]);     // undo the sweeps' scaling
@@ -1102,18 +1105,16 @@ __global__ __launch_bounds__(256) void jacobi_finalize_kernel(const float* Ytb, 
                 static_cast<float>(static_cast<double>(Yt[static_cast<int64_t>(c) * k + i]) / sig[c]);
         }
     }
-    if (tid == 0 && info != nullptr) {
+    if (info != nullptr) {
         // 0: converged; kInfoSweepLimit: none of the nsweeps sweeps run came
         // out rotation-free; kInfoNonFinite: a column norm is NaN or Inf
         // (non-finite input)
         const int* rot = rotb + static_cast<int64_t>(b) * max_sweeps;
-        int result = kInfoSweepLimit;
-        for (int w = 0; w < nsweeps; ++w) {
-            if (rot[w] == 0) { result = 0; break; }
-        }
-        for (int c = 0; c < k; ++c)
-            if (!(sig[c] <= DBL_MAX)) result = kInfoNonFinite;
-        info[b] = result;
+        int bad = 0;
+        for (int c = tid; c < k; c += blockDim.x) bad |= !(sig[c] <= DBL_MAX);
+        const int free_sweep = __syncthreads_or(tid < nsweeps && rot[tid] == 0);
+        bad = __syncthreads_or(bad);
+        if (tid == 0) info[b] = bad ? kInfoNonFinite : (free_sweep ? 0 : kInfoSweepLimit);
     }
     if (nkeep >= r) return;
     // ---- orthonormal completion of columns nkeep .. r-1 (rank-deficient B) ----
@@ -1202,7 +1203,7 @@ hipError_t launch_jacobi_order(const float* Yt, int k, int64_t strideX, double* 
                                int max_sweeps, int sweep, int batch, hipStream_t stream) {
     hipLaunchKernelGGL(jacobi_norms_kernel, dim3((k + 3) / 4, batch), dim3(256), 0, stream, Yt, k, strideX, norms, rot,
                        max_sweeps, sweep);
-    hipLaunchKernelGGL(jacobi_order_kernel, dim3((k + 255) / 256, batch), dim3(256), static_cast<size_t>(k) * sizeof(double),
+    hipLaunchKernelGGL(jacobi_order_kernel, dim3((k + 31) / 32, batch), dim3(256), static_cast<size_t>(k) * sizeof(double),
                        stream, norms, k, jperm, rot, max_sweeps, sweep);
     return hipGetLastError();
 }
@@ -1231,7 +1232,7 @@ hipError_t launch_jacobi_finalize(const float* Yt, int k, int64_t strideX, int r
     hipLaunchKernelGGL(jacobi_norms_kernel, dim3((k + 3) / 4, batch), dim3(256), 0, stream, Yt, k, strideX, norms,
                        static_cast<const int*>(nullptr), 0, 0);
     // their descending order into perm (sweep 0: no convergence check)
-    hipLaunchKernelGGL(jacobi_order_kernel, dim3((k + 255) / 256, batch), dim3(256), static_cast<size_t>(k) * sizeof(double),
+    hipLaunchKernelGGL(jacobi_order_kernel, dim3((k + 31) / 32, batch), dim3(256), static_cast<size_t>(k) * sizeof(double),
                        stream, norms, k, perm, static_cast<const int*>(nullptr), 0, 0);
     const size_t shmem = static_cast<size_t>(k) * (sizeof(double) + sizeof(int));
     hipLaunchKernelGGL(jacobi_finalize_kernel, dim3(batch), dim3(256), shmem, stream, Yt, k, strideX, r, Ur,
