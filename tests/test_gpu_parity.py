@@ -1166,3 +1166,30 @@ def test_bf16_products_tile_forms_agree(gl, m, n, r):
         assert torch.equal(one[0], many[0])
     for many in out[1][:3]:
         assert torch.equal(many[0], many[batch - 1])
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("m,n,r", [(128, 136, 37), (160, 132, 130), (300, 317, 66), (264, 288, 64)])
+def test_quantized_codes_alignment_agrees(gl, bits, m, n, r):
+    """Codes on word boundaries are loaded four at a time, others one by one: the
+    same bits from the projection and the back-projection (ranks off a multiple
+    of four, rows off the tiles, padded and odd row strides)."""
+    import torch
+    s, l = min(m, n), max(m, n)
+    rng = np.random.default_rng(r + bits)
+    G = torch.from_numpy(rng.standard_normal((2, m, n)).astype(np.float32)).cuda().to(torch.bfloat16)
+    N = dev(rng.standard_normal((2, r, l)).astype(np.float32))
+    q = gl.galore_quantize_projector(dev(rng.standard_normal((2, s, r)).astype(np.float32)), bits)
+    cols = q.codes.shape[-1]
+    out = []
+    for off, ldq in ((0, (cols + 11) // 8 * 8), (1, (cols + 11) // 8 * 8), (0, cols | 1), (3, cols + 5)):
+        buf = torch.full((2, s, ldq + off), 0x5A, dtype=torch.uint8, device="cuda")
+        codes = buf[:, :, off:off + cols]
+        codes.copy_(q.codes)
+        W = torch.zeros((2, m, n), device="cuda")
+        qv = type(q)(codes, q.scales, bits, r)
+        R = gl.galore_project_quantized(qv, G)
+        gl.galore_project_back_quantized(qv, N, W, 1.0, 1.0)
+        out.append((R, W))
+    for R, W in out[1:]:
+        assert torch.equal(R, out[0][0]) and torch.equal(W, out[0][1])
