@@ -253,8 +253,9 @@ __device__ __forceinline__ void wait_stages(int ahead) {
 // PA = 3: both operands hold three planes (fp32 x fp32): the six products
 // A_i B_j with i + j <= 4 (planes counted from 1); the three left out are below
 // 2^-26 of |A||B| in size, under fp32 rounding.
-// MB: 32-row blocks per wave (tile of 64 MB rows).
-template <int YK, int S, bool AT, int PA, int PB = 3, int WN = 2, int MB = 4>
+// MB: 32-row blocks per wave (tile of 64 MB rows). RMW: the epilogue that adds
+// to C (beta != 0); the others only store (beta must be 0).
+template <int YK, int S, bool AT, int PA, int PB = 3, int WN = 2, int MB = 4, bool RMW = (PA == 3)>
 __global__ __launch_bounds__(128 * WN, (S * (PA * 64 * MB + PB * 64 * WN) * YK * 2 <= 81920) ? 2 : 1) void gemm_bf16x3_direct_kernel(Bx3Args g) {
     static_assert(!AT || YK == 32, "the M-contiguous A stage assumes 32-deep stages");
     static_assert(PA == 1 || (PA == 3 && !AT), "three A planes are K-contiguous");
@@ -491,16 +492,19 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * 64 * MB + PB * 64 * WN) * YK *
     else if (nb == 1) kloop(std::integral_constant<int, 1>());
     else kloop(std::integral_constant<int, 0>());
 
-    const float alpha = g.alpha, beta = g.beta;
+    const float alpha = g.alpha;
+    [[maybe_unused]] const float beta = g.beta;   // RMW
     unsigned mx[2] = {0u, 0u};   // bits of the largest |C| of this lane's two columns
-    if constexpr (PA == 3) {
-        // the back-projection's read-modify-write of C (W += -lr alpha P N):
+    if constexpr (RMW) {
+        // the back-projections' read-modify-write of C (W += -lr alpha P N):
         // each block's reads of C are issued together before its stores, and
         // a tile that lies inside C (uniform) stores without per-element
         // bounds branches, at whose joins the compiler would wait for the
-        // reads again before every store (38.1 -> 36.4 ms per launch). The
-        // other variants keep the plain epilogue: the longer code measured
-        // slower for them (the sketch product 8.2 against 8.7 ms).
+        // reads again before every store (38.1 -> 36.4 ms per launch; from
+        // a plane of codes, 8 x 4096x4096 at r = 1024, 1245 ->
+        // 960 us). The products that only store keep the plain epilogue: the
+        // longer code measured slower for them (the sketch product 8.2 against
+        // 8.7 ms).
         const bool full_tile = beta != 0.0f && row0 + YM <= M && col0 + YN <= N;
         if (g.c_trans) {
             // C^T: a lane's registers v = 4 q .. 4 q + 3 hold four consecutive m of
@@ -616,16 +620,11 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * 64 * MB + PB * 64 * WN) * YK *
                         f32x4 val = {al * acc[x][y][4 * q], al * acc[x][y][4 * q + 1], al * acc[x][y][4 * q + 2],
                                      al * acc[x][y][4 * q + 3]};
                         if (v4 && r + 4 <= M) {
-                            if (beta != 0.0f) {
-                                const f32x4 old = *reinterpret_cast<const f32x4*>(dst);
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) val[e] += beta * old[e];
-                            }
                             *reinterpret_cast<f32x4*>(dst) = val;
                         } else {
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                if (r + e < M) dst[e] = (beta != 0.0f) ? val[e] + beta * dst[e] : val[e];
+                                if (r + e < M) dst[e] = val[e];
                         }
                     }
                 }
@@ -643,8 +642,7 @@ __global__ __launch_bounds__(128 * WN, (S * (PA * 64 * MB + PB * 64 * WN) * YK *
                     const int r = row0 + wm * (32 * MB) + 32 * x + (v & 3) + 8 * (v >> 2) + 4 * lk;
                     if (r < M && c < N) {
                         float* dst = C + static_cast<int64_t>(r) * g.ldc + c;
-                        float val = al * acc[x][y][v];
-                        if (beta != 0.0f) val += beta * (*dst);
+                        const float val = al * acc[x][y][v];
                         *dst = val;
                         mx[y] = max(mx[y], __float_as_uint(fabsf(val)));
                     }
@@ -801,6 +799,12 @@ hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a
         hipLaunchKernelGGL(kernel, grid, dim3(YT), 0, stream, g);
         return hipGetLastError();
     };
+    if (beta != 0.0f) {
+        // W += codes (three planes of N): the only product of one A plane that adds
+        if (planesB != 3 || a_mcontig) return hipErrorInvalidValue;
+        return half ? run(gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1, 3, 2, 2, true>, 128)
+                    : run(gemm_bf16x3_direct_kernel<kDirectK, kDirectS, false, 1, 3, 2, 4, true>, 256);
+    }
     if (planesB == 1) {
         if (a_mcontig)
             return half ? run(gemm_bf16x3_direct_kernel<32, kDirectST, true, 1, 1, 2, 2>, 128)

@@ -1143,8 +1143,8 @@ def test_fp32_products_tile_forms_agree(gl, m, n, r):
 def test_bf16_products_tile_forms_agree(gl, m, n, r):
     """The bf16 plane products take half-height tiles (three planes) and 128-wide
     tiles (six planes) where a launch has few tiles: the same bits as the wide
-    ones, which a large batch takes (projection, low-bit projection,
-    back-projection and update, both orientations, at and beside the tiles)."""
+    ones, which a large batch takes (projection, back-projection, both with a
+    low-bit projector, and update, both orientations, at and beside the tiles)."""
     import torch
     s, l = min(m, n), max(m, n)
     rng = np.random.default_rng(m * n)
@@ -1158,7 +1158,9 @@ def test_bf16_products_tile_forms_agree(gl, m, n, r):
         W = torch.zeros((b, m, n), device="cuda")
         R = gl.galore_project(Pb[:b], Gb[:b])
         gl.galore_project_back(Pb[:b], Nb[:b], W, 1.0, 1.0)
-        Rq = gl.galore_project_quantized(gl.galore_quantize_projector(Pb[:b]), Gb[:b])
+        q = gl.galore_quantize_projector(Pb[:b])
+        Rq = gl.galore_project_quantized(q, Gb[:b])
+        gl.galore_project_back_quantized(q, Nb[:b], W, 1.0, 1.0)
         Pn, sig, info = gl.galore_rsvd_update(Gb[:b], r, 0, 1, 7)
         assert int(info.max().cpu()) == 0
         out.append((R, W, Rq, Pn, sig))
