@@ -41,7 +41,7 @@ ADAM_BYTES_PER_ELEM = 24      # read R, M, V; write M, V, N (fp32)
 # that run one kernel each, the kernel's symbol and its source file (a stored
 # counter reading is used only while that source is unchanged)
 KERNEL_CLASSES = {
-    "products": (("product_A", "product_At"), "gemm_bf16x3_kernel", "bf16x3.hip"),
+    "products": (("product_A", "product_At"), "gemm_bf16x3_direct_kernel", "bf16x3.hip"),
     "gram": (("gram",), "gram_i8_kernel", "gram_i8.hip"),
     "triangular": (("triangular",), None, "gemm.hip"),
     "projector": (("projector",), None, "gemm.hip"),

@@ -170,7 +170,7 @@ typedef enum {
     GALORE_STAGE_JACOBI = 6,      /* small SVD: all Jacobi sweeps and the sort                  */
     GALORE_STAGE_PROJECTOR = 7,   /* P = Q U_B[:, :r], fp32 matrix cores (1 launch)             */
     GALORE_STAGE_OTHER = 8,       /* small kernels: dependent-column fill, sign convention      */
-    GALORE_STAGE_OPERAND = 9,     /* bf16 G only: transposed copy of G, bf16 split of an fp32    */
+    GALORE_STAGE_OPERAND = 9,     /* bf16 G only: padded copy of G, bf16 split of an fp32        */
                                   /* operand (1 launch each)                                    */
     GALORE_STAGE_REFINE = 10      /* fp64 refinement of the small SVD's vectors                 */
 } galore_stage_t;
