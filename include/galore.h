@@ -390,8 +390,8 @@ GALORE_API size_t galore_project_quantized_workspace_size(int64_t m, int64_t n, 
 /*
  * Projection with the low-bit projector: R = Pq^T A with Pq = code * scale
  * (galore_quantize_projector's codes and scales; paper §3 projection). With a
- * bf16 gradient (16-byte aligned rows and s a multiple of 32, or the padded copy
- * that galore_project describes) the codes form one exact bf16 plane, the product runs once on the bf16 matrix
+ * bf16 gradient (16-byte aligned rows, s a multiple of 32 for m <= n) the
+ * codes form one exact bf16 plane, the product runs once on the bf16 matrix
  * cores with fp32 accumulation and each row of R is multiplied by its scale;
  * otherwise Pq is rounded to fp32 and the product runs on the fp32 matrix
  * cores. Shapes and errors as galore_project, plus those of the codes;

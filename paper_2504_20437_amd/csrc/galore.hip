@@ -803,18 +803,17 @@ struct ProjLayout {
     size_t offGp, totalC;
 };
 
-// planes: 3 (fp32 P) or 1 (codes)
-ProjLayout make_proj_layout(const Shape& sh, int r, int batch, int planes = 3) {
+ProjLayout make_proj_layout(const Shape& sh, int r, int batch) {
     ProjLayout pl;
     pl.ldpl = pad8(sh.s);
     pl.planeStride = pad_elems(static_cast<int64_t>(r) * pl.ldpl);
-    pl.stridePl = planes * pl.planeStride;
+    pl.stridePl = 3 * pl.planeStride;
     pl.total = align_up(static_cast<size_t>(batch) * pl.stridePl * sizeof(uint16_t), kAlign);
     pl.copy = sh.s % 32 != 0 || sh.n % 8 != 0;
     pl.ldplC = pad32(sh.s);
     pl.planeStrideC = pad_elems(static_cast<int64_t>(r) * pl.ldplC);
     pl.strideGp = GradPad(sh).stride;
-    pl.offGp = align_up(static_cast<size_t>(batch) * planes * pl.planeStrideC * sizeof(uint16_t), kAlign);
+    pl.offGp = align_up(static_cast<size_t>(batch) * 3 * pl.planeStrideC * sizeof(uint16_t), kAlign);
     pl.totalC = pl.offGp + align_up(static_cast<size_t>(batch) * pl.strideGp * sizeof(uint16_t), kAlign);
     return pl;
 }
@@ -1159,10 +1158,7 @@ QuantLayout make_quant_layout(const Shape& sh, int r, int batch, bool back) {
 
 size_t galore_project_quantized_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch) {
     if (m < 1 || n < 1 || r < 1 || batch < 1 || m > INT32_MAX || n > INT32_MAX || r > std::min(m, n)) return 0;
-    const Shape sh = make_shape(m, n, r, 0);
-    const ProjLayout pl = make_proj_layout(sh, r, batch, 1);
-    const size_t total = make_quant_layout(sh, r, batch, false).total;
-    return pl.copy ? std::max(total, pl.totalC) : total;
+    return make_quant_layout(make_shape(m, n, r, 0), r, batch, false).total;
 }
 
 size_t galore_project_back_quantized_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch) {
@@ -1201,20 +1197,11 @@ int galore_project_quantized(const uint8_t* Q, int64_t ldq, int64_t stride_q, co
                                           stream, nullptr, 0, 1, scales, ss));
             return GALORE_OK;
         }
-        const ProjLayout pl = make_proj_layout(sh, r, batch, 1);
-        if (pl.copy && workspace_bytes >= pl.totalC) {
-            const GradPad gp(sh);
-            const int ks = static_cast<int>(pl.ldplC);
-            uint16_t* copy = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + pl.offGp);
-            GALORE_TRY(launch_pad_bf16(G, ldg, stride_g, copy, gp.ld, gp.stride, static_cast<int>(m),
-                                       static_cast<int>(n), static_cast<int>(gp.rows), batch, stream));
-            GALORE_TRY(launch_codes_plane(Q, ldq, sq, bits, static_cast<int>(sh.s), r, plane, pl.ldplC,
-                                          pl.planeStrideC, ks, true, batch, stream));
-            GALORE_TRY(launch_gemm_bf16x3(copy, gp.ld, gp.stride, a_mc, plane, pl.ldplC, 0, pl.planeStrideC, R, ldr,
-                                          stride_r, 1, static_cast<int>(sh.l), r, ks, 1.0f, 0.0f, batch, stream,
-                                          nullptr, 0, 1, scales, ss, static_cast<int>(gp.ld)));
-            return GALORE_OK;
-        }
+        // other gradients stay on the fp32 matrix cores: on a padded copy, as
+        // galore_project takes them, the projection is faster, but the other
+        // rounding of R moves 8-bit moment codes on a rounding boundary, 2e-5 of
+        // them, and the next step's N by 1.6e-4 for it. (8 x 2048x5461, r = 512,
+        // 8-bit codes, whole step: 1917 us on this route.)
     }
     float* Pt = static_cast<float*>(workspace);
     GALORE_TRY(launch_dequantize(Q, ldq, sq, bits, scales, ss, static_cast<int>(sh.s), r, Pt, r, ql.strideT, batch,

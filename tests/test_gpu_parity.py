@@ -1062,10 +1062,10 @@ def test_rsvd_cholesky_block_edges(gl, orc, k):
                                                 (31, 300, 301, 3, 7, 8), (257, 40, 45, 1, 33, 4), (128, 264, 272, 5, 32, 8)])
 def test_unaligned_bf16_gradient(gl, orc, m, n, ldg, off, r, bits):
     """bf16 gradients whose rows start on no 16-byte boundary, by size, by row
-    pitch or by the pointer, both orientations: the update, the projection and
-    the low-bit projection through the padded copy, which holds zeros past the
-    matrix (the memory beside G holds NaN), and the projection with a workspace of
-    the planes alone."""
+    pitch or by the pointer, both orientations: the update and the projection
+    through the padded copy, which holds zeros past the matrix (the memory beside
+    G holds NaN), the projection with a workspace of the planes alone, and the
+    low-bit projection on the fp32 matrix cores."""
     import torch
     s, l = min(m, n), max(m, n)
     # sigma's error is of order 2^-24 sigma_1 / sigma_i relative (fp32 products): with
