@@ -11,29 +11,23 @@
 //  * copy_rows: batched strided copy (the previous projector and first moment
 //    kept for the switch inside the scheduled step).
 #include "common.hpp"
+#include "dispatch.hpp"
 
 namespace galore {
 namespace {
-
-// sign_fix and align take 16 columns (64 bytes of a row) a workgroup of 512
-// threads: the scan down the rows waits a memory latency per few rows, so it is
-// split over many threads and the columns over many workgroups (64 columns and
-// 256 threads left one 4096 x 1024 projector to 16 workgroups: 88 us and 209 us;
-// now 32 us and 61 us).
-constexpr int SF_COLS = 16;
-constexpr int SF_GROUPS = 32;
 
 // A workgroup owns SF_COLS columns of one matrix: thread t scans column quad
 // t % SF_QUADS (four columns, one 16-byte load per row when the rows are
 // aligned) over the rows t / SF_QUADS, + SF_RGROUPS, ... in increasing order,
 // four rows in flight; the row groups are reduced through LDS (larger magnitude,
 // then lower row), and the columns whose chosen entry is negative are negated in
-// a second pass with the same access pattern.
-constexpr int SF_QUADS = SF_COLS / 4;
-constexpr int SF_RGROUPS = SF_COLS * SF_GROUPS / SF_QUADS;
-
+// a second pass with the same access pattern. Either form of the workgroup (64
+// columns by 4 groups or 16 by 32) chooses the same entry.
+template <int SF_COLS, int SF_GROUPS>
 __global__ __launch_bounds__(SF_COLS* SF_GROUPS) void sign_fix_kernel(float* Pb, int rows, int r,
                                                                       int64_t ldp, int64_t strideP, int vec) {
+    constexpr int SF_QUADS = SF_COLS / 4;
+    constexpr int SF_RGROUPS = SF_COLS * SF_GROUPS / SF_QUADS;
     const int b = blockIdx.y;
     float* P = Pb + static_cast<int64_t>(b) * strideP;
     const int cq = threadIdx.x % SF_QUADS, rg = threadIdx.x / SF_QUADS;
@@ -120,6 +114,7 @@ __global__ __launch_bounds__(SF_COLS* SF_GROUPS) void sign_fix_kernel(float* Pb,
 // the overlap <p_old_j, p_new_j> is summed in fp64 from the exact fp32
 // products, and column j of the new projector is negated in place when it is
 // negative (zero or NaN keeps the sign; paper §4.1.3 sign indeterminacy).
+template <int SF_COLS, int SF_GROUPS>
 __global__ __launch_bounds__(SF_COLS* SF_GROUPS) void align_kernel(const float* Pob, int64_t ldo, int64_t strideO,
                                                                    float* Pnb, int64_t ldn, int64_t strideN,
                                                                    int rows, int r, int* flipsb) {
@@ -247,18 +242,24 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const float* src, int64_
 
 hipError_t launch_sign_fix(float* P, int rows, int r, int64_t ldp, int64_t strideP, int batch,
                            hipStream_t stream) {
-    dim3 grid((r + SF_COLS - 1) / SF_COLS, batch);
     const int vec = (ldp % 4 == 0) && (batch == 1 || strideP % 4 == 0) && (reinterpret_cast<uintptr_t>(P) % 16 == 0);
-    hipLaunchKernelGGL(sign_fix_kernel, grid, dim3(SF_COLS * SF_GROUPS), 0, stream, P, rows, r, ldp,
-                       strideP, vec);
+    if (narrow_sign_columns(rows, r, batch))
+        hipLaunchKernelGGL((sign_fix_kernel<16, 32>), dim3((r + 15) / 16, batch), dim3(512), 0, stream, P, rows, r, ldp,
+                           strideP, vec);
+    else
+        hipLaunchKernelGGL((sign_fix_kernel<64, 4>), dim3((r + 63) / 64, batch), dim3(256), 0, stream, P, rows, r, ldp,
+                           strideP, vec);
     return hipGetLastError();
 }
 
 hipError_t launch_align(const float* P_old, int64_t ldo, int64_t strideO, float* P_new, int64_t ldn, int64_t strideN,
                         int rows, int r, int* flips, int batch, hipStream_t stream) {
-    dim3 grid((r + SF_COLS - 1) / SF_COLS, batch);
-    hipLaunchKernelGGL(align_kernel, grid, dim3(SF_COLS * SF_GROUPS), 0, stream, P_old, ldo, strideO, P_new, ldn,
-                       strideN, rows, r, flips);
+    if (narrow_align_columns(r, batch))
+        hipLaunchKernelGGL((align_kernel<16, 32>), dim3((r + 15) / 16, batch), dim3(512), 0, stream, P_old, ldo,
+                           strideO, P_new, ldn, strideN, rows, r, flips);
+    else
+        hipLaunchKernelGGL((align_kernel<64, 4>), dim3((r + 63) / 64, batch), dim3(256), 0, stream, P_old, ldo,
+                           strideO, P_new, ldn, strideN, rows, r, flips);
     return hipGetLastError();
 }
 

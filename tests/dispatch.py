@@ -1,0 +1,32 @@
+"""The rules of csrc/dispatch.hpp, compiled for the host: which form of a kernel
+a launch of the given sizes takes."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2504_20437_amd", "csrc")
+
+SHIM = """
+#include "dispatch.hpp"
+using namespace galore;
+extern "C" {
+int narrow_sign_columns_(int rows, int r, long b) { return narrow_sign_columns(rows, r, b); }
+int narrow_align_columns_(int r, long b) { return narrow_align_columns(r, b); }
+}
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        src, out = os.path.join(d, "shim.cpp"), os.path.join(d, "libdispatch.so")
+        with open(src, "w") as f:
+            f.write(SHIM)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, src, "-o", out], check=True)
+        return ctypes.CDLL(out)
+
+
+def rule(name, *args):
+    return getattr(_lib(), name + "_")(*[ctypes.c_long(a) for a in args])

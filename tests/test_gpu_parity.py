@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import galore_inputs as gi
+from dispatch import rule
 from metrics import max_rel_violation, orth_err, proj_dist
 
 pytestmark = pytest.mark.gpu
@@ -1195,3 +1196,51 @@ def test_quantized_codes_alignment_agrees(gl, bits, m, n, r):
         out.append((R, W))
     for R, W in out[1:]:
         assert torch.equal(R, out[0][0]) and torch.equal(W, out[0][1])
+
+
+@pytest.mark.parametrize("s,r", [(1, 1), (31, 17), (33, 16), (1025, 65), (1024, 64)])
+def test_align_column_forms_agree(gl, s, r):
+    """The switch takes 16 columns a workgroup for a few projectors and 64 for
+    many: the same flips and bits, and those of the fp64 overlap where it is
+    clear of rounding (fp64 sums of s exact products: s 2^-53 of their sizes);
+    overlaps of exactly zero and NaN keep the sign."""
+    import torch
+    rng = np.random.default_rng(s * 100 + r)
+    batch = 120
+    assert rule("narrow_align_columns", r, 1) and not rule("narrow_align_columns", r, batch)
+    old = rng.standard_normal((s, r)).astype(np.float32)
+    new = rng.standard_normal((s, r)).astype(np.float32)
+    if r > 2:
+        old[:, 1] = 0.0
+        new[s // 2, 2] = np.nan
+    ov = (old.astype(np.float64) * new).sum(axis=0)
+    clear = np.abs(ov) > s * 2.0 ** -52 * np.abs(old.astype(np.float64) * new).sum(axis=0)
+    out = []
+    for b in (1, batch):
+        Pn = dev(new).expand(b, s, r).contiguous()
+        _, fl, _ = gl.galore_align_projector(dev(old).expand(b, s, r).contiguous(), Pn)
+        out.append((Pn.view(torch.int32), fl.reshape(b, r)))
+    for x, y in zip(*out):
+        for i in (0, batch // 2, batch - 1):
+            assert torch.equal(x[0], y[i])
+    fl = out[0][1][0].cpu().numpy()
+    assert np.array_equal(fl[clear], (ov[clear] < 0).astype(np.int32))
+    assert not fl[~(np.abs(ov) > 0)].any()
+
+
+@pytest.mark.parametrize("m,n,r", [(1024, 1030, 17), (1500, 1027, 16)])
+def test_sign_column_forms_agree(gl, m, n, r):
+    """The sign convention takes 16 columns a workgroup for a few projectors and
+    64 for many: the same bits, the entry of largest magnitude positive."""
+    import torch
+    s, batch = min(m, n), 150
+    assert rule("narrow_sign_columns", s, r, 1) and not rule("narrow_sign_columns", s, r, batch)
+    g = torch.Generator(device="cuda").manual_seed(m)
+    G = torch.randn((m, n), generator=g, device="cuda")
+    P1, _, i1 = gl.galore_rsvd_update(G[None], r, 0, 0, 9)
+    Pb, _, ib = gl.galore_rsvd_update(G.expand(batch, m, n).contiguous(), r, 0, 0, 9)
+    assert int(i1.max().cpu()) == 0 and int(ib.max().cpu()) == 0
+    assert torch.equal(P1[0], Pb[0])
+    for i in (0, batch - 1):
+        top = Pb[i].abs().argmax(dim=0)
+        assert (Pb[i].gather(0, top[None]) > 0).all()
