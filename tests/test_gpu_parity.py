@@ -1244,3 +1244,64 @@ def test_sign_column_forms_agree(gl, m, n, r):
     for i in (0, batch - 1):
         top = Pb[i].abs().argmax(dim=0)
         assert (Pb[i].gather(0, top[None]) > 0).all()
+
+
+def _padded_projection(gl, m, n, r, batch, ldg=None, off=0):
+    """galore_project of a bf16 gradient off the 16-byte grid, NaN beside it,
+    against fp64 (fp32 accumulation of s products: s 2^-24 of the sum of their
+    sizes, and a few ulps more)."""
+    import torch
+    s, ldg = min(m, n), ldg or n
+    gen = torch.Generator(device="cuda").manual_seed(m + 3 * n)
+    buf = torch.full((batch * m * ldg + off + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    G = torch.as_strided(buf, (batch, m, n), (m * ldg, ldg, 1), off)
+    G.copy_(torch.randn((batch, m, n), generator=gen, device="cuda"))
+    P = torch.randn((batch, s, r), generator=gen, device="cuda")
+    R = gl.galore_project(P, G)
+    for i in {0, batch - 1}:
+        A = (G[i] if m <= n else G[i].T).double()
+        ref = P[i].double().T.contiguous() @ A.contiguous()
+        bound = (s * 2.0 ** -24 + 2.0 ** -22) * (P[i].double().abs().T.contiguous() @ A.abs().contiguous())
+        assert bool(((R[i].double() - ref).abs() <= bound).all())
+    return P, G, R
+
+
+@pytest.mark.parametrize("width", [1, 31, 33, 65, 129, 257, 513, 1025, 2049, 4100])
+@pytest.mark.parametrize("tall", [True, False])
+def test_padded_copy_row_widths(gl, width, tall):
+    """The padded copy deals a workgroup's threads out over rows by the row's
+    width: every number of threads a row, rows off the workgroup's, both
+    orientations, a pitch and a pointer off the word."""
+    rows = {True: max(width + 70, 200), False: max(1, min(width // 2, 77))}[tall]
+    r = min(width, rows, 5)
+    _padded_projection(gl, rows, width, r, 2)
+    _padded_projection(gl, rows, width, r, 2, ldg=width + 3, off=1)
+
+
+def test_padded_copy_past_one_grid(gl):
+    """More rows than a grid axis holds groups of them (65535 groups of 64)."""
+    _padded_projection(gl, 65535 * 64 + 77, 9, 2, 1)
+
+
+def test_padded_copy_of_thin_rows_fills_the_chip(gl):
+    """Device time of the projection of thin matrices stored by long columns
+    against the same stored by long rows: 1.15 times, 5 times with a workgroup
+    a row of the copy."""
+    import torch
+    times = []
+    for m, n in ((50001, 16), (16, 50001)):
+        G = torch.zeros((8, m, n), dtype=torch.bfloat16, device="cuda")
+        P = torch.zeros((8, 16, 4), device="cuda")
+        R = torch.empty((8, 4, 50001), device="cuda")
+        ws = torch.empty((gl.galore_project_workspace_size(m, n, 4, 8, G.dtype),), dtype=torch.uint8, device="cuda")
+        best = 1e9
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                gl.galore_project(P, G, R=R, workspace=ws)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    assert times[0] < 2.5 * times[1]
