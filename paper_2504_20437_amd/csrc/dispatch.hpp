@@ -26,4 +26,49 @@ inline bool narrow_align_columns(int r, int64_t batch) {
     return static_cast<int64_t>((r + 63) / 64) * batch < 112;
 }
 
+// Tiles of the fp32 products (gemm.hip): 128 x 128 x 32, two workgroups to a CU;
+// 64 x 64 x 64, two to a CU; 64 x 64 x 32, four to a CU. With T wide and t narrow
+// tiles (T counts padding, t much less of it):
+//  * t <= 512, one round of two to a CU: the deep narrow tile, half the stages,
+//    each of which waits a memory latency (A Omega of 8 x 1024x1024, k = 136:
+//    deep 115, shallow 123, wide 187 us; at t = 576: 172, 153, 202);
+//  * else the shallow narrow tile: its rounds are finer (7 x 1024x1024, k = 272,
+//    T = 168, t = 560: deep 178, shallow 153, wide 202; T = 528: 399, 360, 448);
+//  * but the wide one where its rounds of 512 are full but for an eighth by t (a
+//    fifth where rows of A run along K: their narrow tiles cost more, N = k being
+//    seldom a multiple of 64): the narrow tiles stage every operand twice as often
+//    (projection, K = 2048, T = t / 4 = 420: 277 narrow, 281 wide; 480: 311, 282;
+//    508: 315, 283; 516: 362, 454; 860: 548, 557; 900: 587, 557; 1016: 630, 566;
+//    A X, K = 2736, t / 4 = 400: 859, 833; 420: 895, 833; 800: 1581, 1597; 840:
+//    1645, 1629), unless the product adds to C, whose reads four workgroups a CU
+//    hide better (K = 128, T = 512: 37 narrow, 44 wide; 1016: 68, 83; K = 512,
+//    1016: 175, 181);
+//  * past 1280 wide tiles, two and a half rounds, always the wide one (2 x
+//    4096x11008, r = 1024, T = 1376: 1840 narrow, 1779 wide; K = 512, T = 1500:
+//    249, 228).
+enum F32Tile { kTile128, kTile64, kTile64x4 };
+inline int64_t f32_tiles(int M, int N, int tile, int64_t batch) {
+    return static_cast<int64_t>((N + tile - 1) / tile) * ((M + tile - 1) / tile) * batch;
+}
+inline F32Tile f32_tile(int M, int N, bool a_kcontig, bool adds, int64_t batch) {
+    const int64_t wide = f32_tiles(M, N, 128, batch), narrow = f32_tiles(M, N, 64, batch);
+    if (wide > 1280) return kTile128;
+    if (narrow <= 512) return kTile64;
+    const int64_t rounds = (wide + 511) / 512;
+    const int64_t full = 4 * 512 * rounds;
+    if (!adds && (a_kcontig ? 5 * narrow > 4 * full : 8 * narrow > 7 * full)) return kTile128;
+    return kTile64x4;
+}
+// The triangular product Y R^-1 (fp32 output): the wide tile's 4 x 1 waves or the
+// deep narrow tile. The launch ends with the longest column tile, K deep, and the
+// narrow tiles' extra rounds fill its time the better the larger K is: k = 72, t =
+// 512: 48 narrow, 65 wide, t = 1024: 82, 69; k = 136, t = 576: 62, 71, t = 624: 80,
+// 71; k = 272, t = 960: 125, 133, t = 1040: 144, 136, t = 1680: 199, 148; k = 528,
+// t = 1728: 274, 279, t = 2016: 334, 295; k = 1056, t = 1596: 448, 474.
+inline F32Tile f32_tril_tile(int M, int N, int K, int64_t batch) {
+    const int64_t wide = f32_tiles(M, N, 128, batch), narrow = f32_tiles(M, N, 64, batch);
+    const int64_t deep = static_cast<int64_t>(K) * 18 / 5;   // 3.6 K
+    return wide <= 512 && narrow <= (deep > 608 ? deep : 608) ? kTile64 : kTile128;
+}
+
 }  // namespace galore

@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "dispatch.hpp"
 
 namespace galore {
 namespace {
@@ -21,10 +22,9 @@ namespace {
 constexpr int NT = 256;
 
 // Workgroup tiles: 128 x 128 x 32 (2 x 2 waves of 64 x 64, two workgroups per
-// CU), 64 x 64 x 64 (2 x 2 waves of 32 x 32, two per CU) where a launch has too
-// few of the former to fill the chip, and 64 x 64 x 32 (four per CU). All take
-// the contraction in the same order, so the results are the same bits.
-enum Tile { kTile128, kTile64, kTile64x4 };
+// CU), 64 x 64 x 64 (2 x 2 waves of 32 x 32, two per CU) and 64 x 64 x 32 (four
+// per CU), chosen by the rules of dispatch.hpp. All take the contraction in the
+// same order, so the results are the same bits.
 template <int TS>
 struct TileShape {
     static constexpr int BM = TS == kTile128 ? 128 : 64;
@@ -395,21 +395,6 @@ __global__ __launch_bounds__(NT, TileShape<TS>::PER_CU) void gemm_f32_kernel(Gem
     }
 }
 
-// 128-wide tiles up to which a launch takes the 64-wide ones instead: two
-// workgroups of the wide tile share a CU, so up to 512 of them the launch lasts
-// as long as one of them alone, and waits a memory latency per 32-deep stage.
-// The 64-wide tiles bring four times the workgroups and half the stages:
-// A Omega of 16 x 512x1376 (k = 136, 48 wide tiles) 118 -> 74 us, of 6 x
-// 1024x2736 (k = 272, 144) 250 -> 156 us, of one 256x688 (k = 40, 2) 71 -> 26 us;
-// equal at 1056 wide tiles (24 x 2736x1024, r = 256).
-constexpr int64_t kSmallTiles = 512;
-// and up to which it takes 64-wide tiles of half the depth, four to a CU: the
-// wide ones' last round, of 512, is then mostly empty (projections of 24 x
-// 2736x1024, r = 256, 1056 wide tiles: 442 -> 415 us; of 16 x 3000x1500, r = 300,
-// 1152: 566 -> 460 us; of 2 x 4096x11008, r = 1024, 1376: 1779 -> 1840 us, of 2 x
-// 11008x4096 equal). The triangular product keeps the wide tile's 4 x 1 waves.
-constexpr int64_t kMidTiles = 1280;
-
 template <int TS, ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
 hipError_t launch_tile(const GemmArgs& g, int batch, hipStream_t stream) {
     constexpr int T = TileShape<TS>::BM;
@@ -427,12 +412,13 @@ hipError_t launch_tile(const GemmArgs& g, int batch, hipStream_t stream) {
 
 template <ALayout LA, BLayout LB, typename TA, typename TB, bool PLANES = false, bool TRIL = false>
 hipError_t launch_one(const GemmArgs& g, int batch, hipStream_t stream) {
-    if constexpr (!PLANES) {
-        const int64_t tiles = static_cast<int64_t>((g.N + 127) / 128) * ((g.M + 127) / 128) * batch;
-        if (tiles <= kSmallTiles) return launch_tile<kTile64, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
-        if constexpr (!TRIL) {
-            if (tiles <= kMidTiles) return launch_tile<kTile64x4, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
-        }
+    if constexpr (TRIL && !PLANES) {
+        if (f32_tril_tile(g.M, g.N, g.K, batch) == kTile64)
+            return launch_tile<kTile64, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+    } else if constexpr (!PLANES) {
+        const F32Tile tile = f32_tile(g.M, g.N, LA == ALayout::kKContig, g.beta != 0.0f, batch);
+        if (tile == kTile64) return launch_tile<kTile64, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
+        if (tile == kTile64x4) return launch_tile<kTile64x4, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
     }
     return launch_tile<kTile128, LA, LB, TA, TB, PLANES, TRIL>(g, batch, stream);
 }

@@ -1108,10 +1108,10 @@ def test_unaligned_bf16_gradient(gl, orc, m, n, ldg, off, r, bits):
 
 @pytest.mark.parametrize("m,n,r", [(64, 64, 64), (65, 130, 33), (129, 63, 40), (200, 257, 100)])
 def test_fp32_products_tile_forms_agree(gl, m, n, r):
-    """The fp32 products take 64-wide tiles up to 512 wide ones a launch, 64-wide
-    ones of half the depth up to 1280 and the wide ones above: the same bits
-    (projection and back-projection, both orientations, sizes at and beside the
-    tiles), and against host fp64."""
+    """The fp32 products take deep narrow tiles for the smallest launches, wide
+    ones where they fill their rounds or are many, shallow narrow ones else: the
+    same bits (projection and back-projection, both orientations, sizes at and
+    beside the tiles; batches of each form by the rule), and against host fp64."""
     import torch
     s, l = min(m, n), max(m, n)
     rng = np.random.default_rng(m + n)
@@ -1121,16 +1121,24 @@ def test_fp32_products_tile_forms_agree(gl, m, n, r):
     W1 = torch.zeros((1, m, n), device="cuda")
     R1 = gl.galore_project(dev(P)[None], dev(G)[None])
     gl.galore_project_back(dev(P)[None], dev(N)[None], W1, 1.0, 1.0, workspace=False)
-    tiles = -(-r // 128) * -(-l // 128), -(-m // 128) * -(-n // 128)
-    for want in (900, 1300):   # wide tiles a launch: the middle form, the wide one
-        for t in set(tiles):
-            batch = want // t + 1
-            Gb, Pb, Nb = (dev(x).expand(batch, *x.shape).contiguous() for x in (G, P, N))
-            Wb = torch.zeros((batch, m, n), device="cuda")
-            Rb = gl.galore_project(Pb, Gb)
-            gl.galore_project_back(Pb, Nb, Wb, 1.0, 1.0, workspace=False)
-            for i in (0, batch - 1):
-                assert torch.equal(R1[0], Rb[i]) and torch.equal(W1[0], Wb[i])
+
+    def batches(M, N, kcontig, adds):
+        # the first batch of the other forms, and one past 1280 wide tiles
+        form = [rule("f32_tile", M, N, kcontig, adds, b) for b in range(1, 1400)]
+        assert form[0] == 1 and form[-1] == 0
+        return [form.index(0) + 1, form.index(2) + 1, 1399]
+
+    for batch in batches(r, l, 0, 0):
+        Gb, Pb = (dev(x).expand(batch, *x.shape).contiguous() for x in (G, P))
+        Rb = gl.galore_project(Pb, Gb)
+        for i in (0, batch - 1):
+            assert torch.equal(R1[0], Rb[i])
+    for batch in batches(m, n, int(m <= n), 1):
+        Pb, Nb = (dev(x).expand(batch, *x.shape).contiguous() for x in (P, N))
+        Wb = torch.zeros((batch, m, n), device="cuda")
+        gl.galore_project_back(Pb, Nb, Wb, 1.0, 1.0, workspace=False)
+        for i in (0, batch - 1):
+            assert torch.equal(W1[0], Wb[i])
     A = G.astype(np.float64) if m <= n else G.T.astype(np.float64)
     P64, N64 = P.astype(np.float64), N.astype(np.float64)
     # fp32 accumulation: as many roundings as terms, of the sum of their sizes
