@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "dispatch.hpp"
 
 namespace galore {
 namespace {
@@ -698,27 +699,6 @@ constexpr int kX6K = GALORE_BX6_K;         // K depth of a stage
 constexpr int kX6S = GALORE_BX6_S;         // stages in LDS
 constexpr int kX6WN = GALORE_BX6_WN;       // waves across N (tile 256 x 64 WN)
 
-// 128-row tiles instead of 256-row ones where the latter leave CUs idle. One
-// 4096x11008 matrix (144 wide tiles): the sketch product 246 -> 191 us, A X 467
-// -> 439 us; with every CU taken the half tiles lose, staging B twice as often
-// (344 wide tiles, the projection of one 11008x4096: 332 against 372 us).
-bool half_tiles(int M, int N, int tile_n, int batch) {
-    return static_cast<int64_t>((N + tile_n - 1) / tile_n) * ((M + 255) / 256) * batch <= 256;
-}
-
-// The six-plane product on 128 x 128 tiles, two workgroups per CU, instead of 256
-// x 256, one per CU: whole rounds of tiles over the chip, the smaller ones at
-// 1.3 times the cost for the same work (11008x4096, r = 1024, 688 wide tiles: 640
-// against 839 us). They win where the wide tiles fill the chip badly: one
-// 512x1376, r = 128 (12 wide tiles) 36 -> 17 us, a 4096 x 1024 projector (64) 147
-// -> 76 us, 6 x 1024x2736, r = 256 (264, one past a round) 120 -> 95 us; not at
-// 1056 (24 x 2736x1024, 343 against 360 us).
-bool six_plane_small(int M, int N, int batch) {
-    const int64_t wide = static_cast<int64_t>((N + 255) / 256) * ((M + 255) / 256) * batch;
-    const int64_t small = static_cast<int64_t>((N + 127) / 128) * ((M + 127) / 128) * batch;
-    return 13 * ((small + 511) / 512) < 20 * ((wide + 255) / 256);
-}
-
 }  // namespace
 
 hipError_t launch_pad_bf16(const void* src, int64_t lds, int64_t strideS, void* dst, int64_t ldd, int64_t strideD,
@@ -801,7 +781,8 @@ hipError_t launch_gemm_bf16x3(const void* A, int64_t lda, int64_t strideA, int a
     if (!bf16x3_direct_ok(A, lda, strideA, Bplanes, ldb, planeStride, strideB, g.mload, K, batch, a_mcontig) ||
         (a_mcontig && g.mload < M))
         return hipErrorInvalidValue;
-    const bool half = half_tiles(M, N, YN, batch);
+    const bool half = three_plane_half(M, N, batch);
+    static_assert(YN == 128, "the rule counts tiles of 128 columns");
     auto run = [&](auto kernel, int tile_m) {
         dim3 grid((N + YN - 1) / YN, (M + tile_m - 1) / tile_m, batch);
         hipLaunchKernelGGL(kernel, grid, dim3(YT), 0, stream, g);
@@ -877,7 +858,7 @@ hipError_t launch_gemm_bf16x6(const void* Aplanes, int64_t lda, int64_t planeStr
     g.b_upper = b_upper;
     g.cmax = nullptr;
     g.strideCM = 0;
-    if (six_plane_small(M, N, batch)) {
+    if (six_plane_small(M, N, K, batch)) {
         dim3 grid((N + 127) / 128, (M + 127) / 128, batch);
         hipLaunchKernelGGL((gemm_bf16x3_direct_kernel<kX6K, kX6S, false, 3, 3, 2, 2>), grid, dim3(256), 0, stream, g);
         return hipGetLastError();

@@ -8,6 +8,10 @@
 
 namespace galore {
 
+inline int64_t tile_count(int M, int N, int tile_m, int tile_n, int64_t batch) {
+    return static_cast<int64_t>((N + tile_n - 1) / tile_n) * ((M + tile_m - 1) / tile_m) * batch;
+}
+
 // The column scans of a projector (sign convention, switch): workgroups of 16
 // columns and 512 threads instead of 64 columns and 256, while the latter would
 // leave CUs idle. A 16-column workgroup reads 64-byte pieces of rows and moves
@@ -47,11 +51,8 @@ inline bool narrow_align_columns(int r, int64_t batch) {
 //    4096x11008, r = 1024, T = 1376: 1840 narrow, 1779 wide; K = 512, T = 1500:
 //    249, 228).
 enum F32Tile { kTile128, kTile64, kTile64x4 };
-inline int64_t f32_tiles(int M, int N, int tile, int64_t batch) {
-    return static_cast<int64_t>((N + tile - 1) / tile) * ((M + tile - 1) / tile) * batch;
-}
 inline F32Tile f32_tile(int M, int N, bool a_kcontig, bool adds, int64_t batch) {
-    const int64_t wide = f32_tiles(M, N, 128, batch), narrow = f32_tiles(M, N, 64, batch);
+    const int64_t wide = tile_count(M, N, 128, 128, batch), narrow = tile_count(M, N, 64, 64, batch);
     if (wide > 1280) return kTile128;
     if (narrow <= 512) return kTile64;
     const int64_t rounds = (wide + 511) / 512;
@@ -66,9 +67,34 @@ inline F32Tile f32_tile(int M, int N, bool a_kcontig, bool adds, int64_t batch) 
 // 71; k = 272, t = 960: 125, 133, t = 1040: 144, 136, t = 1680: 199, 148; k = 528,
 // t = 1728: 274, 279, t = 2016: 334, 295; k = 1056, t = 1596: 448, 474.
 inline F32Tile f32_tril_tile(int M, int N, int K, int64_t batch) {
-    const int64_t wide = f32_tiles(M, N, 128, batch), narrow = f32_tiles(M, N, 64, batch);
+    const int64_t wide = tile_count(M, N, 128, 128, batch), narrow = tile_count(M, N, 64, 64, batch);
     const int64_t deep = static_cast<int64_t>(K) * 18 / 5;   // 3.6 K
     return wide <= 512 && narrow <= (deep > 608 ? deep : 608) ? kTile64 : kTile128;
+}
+
+// The products of one or three bf16 planes (bf16x3.hip), two workgroups to a CU:
+// 128 x 128 tiles instead of 256 x 128 up to 256 of the latter, which as half tiles
+// are one round of 512. Past it the half tiles begin a second round and stage B
+// twice as often (projection, three planes, r = 1024, s = 4096, wide / half: 176
+// tiles: 177 / 175 us, 248: 197 / 194, 264: 252 / 299, 512: 315 / 372; r = 128, s =
+// 512: 100: 32 / 26, 250: 38 / 36, 262: 46 / 51; the sketch product of one
+// 4096x11008, 144: 246 / 191; low-bit back-projection, r = 1024, 248: 70 / 68,
+// 264: 91 / 99).
+inline bool three_plane_half(int M, int N, int64_t batch) { return tile_count(M, N, 256, 128, batch) <= 256; }
+
+// The six-plane product: 128 x 128 tiles, two workgroups to a CU (rounds of 512),
+// instead of 256 x 256, one to a CU (rounds of 256). For the same work the small
+// tiles cost 1.3 times as much at K = 256 and, half round by half round, 1.4 times
+// at larger K; they win where the wide ones leave their last round nearly empty
+// (back-projection, small / wide tiles, us; T wide ones): K = 1024, T = 64: 80 /
+// 145, 128: 137 / 154, 152: 178 / 154, 260: 303 / 333, 320: 339 / 352, 352: 386 /
+// 357, 384: 409 / 367, 520: 572 / 559; K = 512, 320: 179 / 191, 352: 206 / 194; K =
+// 256, 320: 103 / 118, 352: 113 / 117, 420: 129 / 121, 688: 229 / 208; K = 64, 384:
+// 59 / 63, 508: 75 / 73).
+inline bool six_plane_small(int M, int N, int K, int64_t batch) {
+    const int64_t wide = tile_count(M, N, 256, 256, batch), small = tile_count(M, N, 128, 128, batch);
+    const int64_t cost = K <= 256 ? 13 * ((small + 511) / 512) : 7 * ((small + 255) / 256);
+    return cost < 20 * ((wide + 255) / 256);
 }
 
 }  // namespace galore
