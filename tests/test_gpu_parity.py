@@ -1148,35 +1148,61 @@ def test_fp32_products_tile_forms_agree(gl, m, n, r):
     assert np.all(np.abs(host(W1)[0] + D) <= (r + 4) * 2.0 ** -24 * (Db if m <= n else Db.T))
 
 
-@pytest.mark.parametrize("m,n,r", [(128, 136, 32), (136, 128, 64), (264, 160, 96), (160, 520, 32)])
-def test_bf16_products_tile_forms_agree(gl, m, n, r):
+@pytest.mark.parametrize("m,n,r,six", [(128, 136, 32, False), (136, 128, 64, False), (264, 160, 96, True),
+                                       (160, 520, 32, True), (160, 224, 144, True), (224, 160, 144, True)])
+def test_bf16_products_tile_forms_agree(gl, m, n, r, six):
     """The bf16 plane products take half-height tiles (three planes) and 128-wide
     tiles (six planes) where a launch has few tiles: the same bits as the wide
-    ones, which a large batch takes (projection, back-projection, both with a
-    low-bit projector, and update, both orientations, at and beside the tiles)."""
+    ones, which a batch of the size the rules name takes (projection,
+    back-projection, both with a low-bit projector, and the projector of an
+    update, both orientations, at and beside the tiles). Where six is False the
+    six-plane product takes small tiles in every batch (its wide tile would be
+    half padding)."""
     import torch
     s, l = min(m, n), max(m, n)
     rng = np.random.default_rng(m * n)
-    batch = 600
     G = torch.from_numpy(rng.standard_normal((m, n)).astype(np.float32)).cuda().to(torch.bfloat16)
     P = dev(np.linalg.qr(rng.standard_normal((s, r)))[0].astype(np.float32))
     N = dev(rng.standard_normal((r, l)).astype(np.float32))
-    Gb, Pb, Nb = (x.expand(batch, *x.shape).contiguous() for x in (G, P, N))
-    out = []
-    for b in (1, batch):
+
+    def project(b):
+        return gl.galore_project(P.expand(b, s, r).contiguous(), G.expand(b, m, n).contiguous())
+
+    def project_low(b):
+        return gl.galore_project_quantized(gl.galore_quantize_projector(P.expand(b, s, r).contiguous()),
+                                           G.expand(b, m, n).contiguous())
+
+    def back(b):
         W = torch.zeros((b, m, n), device="cuda")
-        R = gl.galore_project(Pb[:b], Gb[:b])
-        gl.galore_project_back(Pb[:b], Nb[:b], W, 1.0, 1.0)
-        q = gl.galore_quantize_projector(Pb[:b])
-        Rq = gl.galore_project_quantized(q, Gb[:b])
-        gl.galore_project_back_quantized(q, Nb[:b], W, 1.0, 1.0)
-        Pn, sig, info = gl.galore_rsvd_update(Gb[:b], r, 0, 1, 7)
+        return gl.galore_project_back(P.expand(b, s, r).contiguous(), N.expand(b, r, l).contiguous(), W, 1.0, 1.0)
+
+    def back_low(b):
+        W = torch.zeros((b, m, n), device="cuda")
+        return gl.galore_project_back_quantized(gl.galore_quantize_projector(P.expand(b, s, r).contiguous()),
+                                                N.expand(b, r, l).contiguous(), W, 1.0, 1.0)
+
+    def update(b):
+        Pn, sig, info = gl.galore_rsvd_update(G.expand(b, m, n).contiguous(), r, 0, 1, 7)
         assert int(info.max().cpu()) == 0
-        out.append((R, W, Rq, Pn, sig))
-    for one, many in zip(*out):
+        return torch.cat([Pn.reshape(b, -1), sig], dim=1)
+
+    def batch_of_wide(name, *args):
+        form = [rule(name, *args, b) for b in range(1, 1001)]
+        assert form[0]
+        return form.index(0) + 1
+
+    runs = [(project, batch_of_wide("three_plane_half", l, r)), (project_low, batch_of_wide("three_plane_half", l, r)),
+            (back_low, batch_of_wide("three_plane_half", s, l))]
+    if six:
+        runs.append((back, batch_of_wide("six_plane_small", s, l, r)))
+    if six and r == 144:
+        # matrix 0 of a batch draws the single call's sketch
+        runs.append((update, batch_of_wide("six_plane_small", s, r, r)))
+    for run, batch in runs:
+        one, many = run(1), run(batch)
         assert torch.equal(one[0], many[0])
-    for many in out[1][:3]:
-        assert torch.equal(many[0], many[batch - 1])
+        if run is not update:
+            assert torch.equal(many[0], many[batch - 1])
 
 
 @pytest.mark.parametrize("bits", [8, 4])
