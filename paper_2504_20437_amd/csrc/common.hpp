@@ -152,7 +152,8 @@ hipError_t launch_jacobi_prepare(const double* R, int k, int64_t strideR, float*
 hipError_t launch_jacobi_order(const float* Yt, int k, int64_t strideX, double* norms, int* jperm, const int* rot,
                                int max_sweeps, int sweep, int batch, hipStream_t stream);
 hipError_t launch_jacobi_step(float* Yt, int k, int64_t strideX, int nblocks, int step, int sweep, int* rot,
-                              int max_sweeps, double tol, const int* jperm, int batch, hipStream_t stream);
+                              int max_sweeps, double tol, const int* jperm, int batch, int in_flight,
+                              hipStream_t stream);
 // scratch: at least 2 k + r doubles per matrix at stride strideScratch (doubles);
 // exps: the per-matrix exponents launch_jacobi_prepare wrote (sigma = 2^-e |y|);
 // norms (k fp64) and perm (k int) per matrix: scratch for the column norms and

@@ -97,4 +97,25 @@ inline bool six_plane_small(int M, int N, int K, int64_t batch) {
     return cost < 20 * ((wide + 255) / 256);
 }
 
+// A step of the small SVD (jacobi.hip): four groups of waves a workgroup, one
+// workgroup to a CU, or one group, four to a CU. `batch` matrices in this launch,
+// `in_flight` with those of the launch that runs beside it on the second stream.
+// On one stream the wide form wins as long as its workgroups have a CU each (k =
+// 1056, whole stage, 16 matrices, 256 workgroups: 18.9 against 24.5 ms; k = 528,
+// 256: 7.2, 8.3; k = 136, 240: 1.40, 1.44). Two halves on two streams are seldom in
+// the same phase, so a few more than 256 in all still gain, the more the longer
+// the chunk loops are (k = 1056, 272: 21.6, 25.6 ms; 352: 24.9, 26.6; 384: 24.9,
+// 25.9; 448: 29.2, 27.9; 512: 31.1, 28.1; k = 528, 320: 8.5, 8.7; 384: 9.5, 8.9; k
+// = 136, 260: 2.7, 2.8; 300: 1.71, 1.64; k = 40, 300: 0.48, 0.43; k = 2048, 480:
+// 84.0, 88.4; 512: 94.5, 88.7).
+// (pairs of a step of k columns in blocks: an odd number of blocks, at least three,
+// has a padding block, whose pair is not launched)
+inline int step_pairs(int k, int block) {
+    const int real = (k + block - 1) / block;
+    return real % 2 != 0 && real >= 3 ? real / 2 : (real + 1) / 2;
+}
+inline bool wide_pairs(int k, int pairs, int64_t batch, int64_t in_flight) {
+    return pairs * batch <= 256 && pairs * in_flight <= 256 + (k < 1792 ? k : 1792) / 8;
+}
+
 }  // namespace galore

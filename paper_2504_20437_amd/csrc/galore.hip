@@ -406,7 +406,7 @@ int enqueue_jacobi_sweeps(float* Yt, int k, int64_t strideKK, int nb, int* rot, 
                                            rot + b0 * kMaxSweeps, kMaxSweeps, sw, cnt, st));
             for (int stp = 0; stp < nb - 1; ++stp)
                 GALORE_TRY(launch_jacobi_step(Yt + b0 * strideKK, k, strideKK, nb, stp, sw, rot + b0 * kMaxSweeps,
-                                              kMaxSweeps, kJacobiTol, jperm + ko, cnt, st));
+                                              kMaxSweeps, kJacobiTol, jperm + ko, cnt, batch, st));
         }
         return GALORE_OK;
     });

@@ -43,6 +43,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "dispatch.hpp"
 
 namespace galore {
 namespace {
@@ -51,7 +52,6 @@ constexpr int JB = kJacobiBlock;   // columns per block
 constexpr int JW = 2 * JB;         // columns per pair (64)
 constexpr int JT = 256;            // threads (4 waves)
 constexpr int PD = JW + 1;         // padded LDS row
-constexpr int kPairWideMax = 256;  // workgroups up to which a step's launch takes the wide form (the CUs)
 
 static_assert(JW == 64, "the pair kernels assume 64 columns per pair");
 
@@ -657,8 +657,8 @@ __device__ __forceinline__ void inner_sweep(unsigned char* smem, int wave, int l
 // Step of the block Jacobi (one workgroup per pair and matrix): Gram of the
 // pair's 64 columns, convergence test, reduction of the small Gram, rotation
 // of the columns, all in one LDS buffer per group of four waves (see above).
-// NG groups: 1, four workgroups per CU; or 4 (one workgroup per CU), for
-// launches whose workgroups do not outnumber the CUs: the chunk loops of the
+// NG groups: 1, four workgroups per CU; or 4 (one workgroup per CU), for steps
+// of few workgroups (wide_pairs in dispatch.hpp): the chunk loops of the
 // two phases over memory wait a memory latency per chunk, which only other
 // workgroups of the CU would hide, so four groups walk a quarter of the chunks
 // each. The results are the same bits. One 4096x11008 update (k = 1056, 16
@@ -1209,13 +1209,11 @@ hipError_t launch_jacobi_order(const float* Yt, int k, int64_t strideX, double* 
 }
 
 hipError_t launch_jacobi_step(float* Yt, int k, int64_t strideX, int nblocks, int step, int sweep, int* rot,
-                              int max_sweeps, double tol, const int* jperm, int batch, hipStream_t stream) {
-    // an odd number of real blocks (at least 3) leaves one padding block
-    const int nreal = (k + JB - 1) / JB;
-    const int skip_dummy = (nblocks > nreal && nreal >= 3) ? 1 : 0;
-    const int pairs = nblocks / 2 - skip_dummy;
-    // at most one workgroup per CU: four groups of waves each
-    if (static_cast<int64_t>(pairs) * batch <= kPairWideMax)
+                              int max_sweeps, double tol, const int* jperm, int batch, int in_flight,
+                              hipStream_t stream) {
+    const int pairs = step_pairs(k, JB);
+    const int skip_dummy = nblocks / 2 - pairs;   // the padding block's pair
+    if (wide_pairs(k, pairs, batch, in_flight))
         hipLaunchKernelGGL(jacobi_pair_kernel<4>, dim3(pairs, batch), dim3(4 * JT), 0, stream, Yt, k, strideX, nblocks,
                            step, sweep, rot, max_sweeps, tol, skip_dummy, jperm);
     else

@@ -18,6 +18,8 @@ int f32_tile_(int M, int N, int kcontig, int adds, long b) { return f32_tile(M, 
 int f32_tril_tile_(int M, int N, int K, long b) { return f32_tril_tile(M, N, K, b); }
 int three_plane_half_(int M, int N, long b) { return three_plane_half(M, N, b); }
 int six_plane_small_(int M, int N, int K, long b) { return six_plane_small(M, N, K, b); }
+int step_pairs_(int k, int block) { return step_pairs(k, block); }
+int wide_pairs_(int k, int pairs, long b, long in_flight) { return wide_pairs(k, pairs, b, in_flight); }
 }
 """
 

@@ -1024,18 +1024,23 @@ def test_rsvd_pair_launch_forms_agree(gl, orc, k):
     spec[r:] *= 0.1
     G = gi.store(gi.planted_gradient(m, n, spec, 1e-6, seed=k), "f32")
     _check_rsvd(gl, orc, G, r, k - r, 1, seed=21, idx=0)
-    # pairs of 32-column blocks a step; the padding block of an odd number is not launched
-    nreal = (k + 31) // 32
-    pairs = (nreal + 1) // 2 - (1 if nreal % 2 and nreal >= 3 else 0)
-    pairs = max(1, pairs)
+    pairs = rule("step_pairs", k, 32)
     batch = 256 // pairs + 1
-    assert pairs <= 256 < pairs * batch
+    assert rule("wide_pairs", k, pairs, 1, 1) and not rule("wide_pairs", k, pairs, batch, batch)
     Gb = dev_stored(G).expand(batch, m, n).contiguous()
     Pw, sw, iw = gl.galore_rsvd_update(Gb[:1].contiguous(), r, k - r, 1, 21, 0)
     # every matrix draws its own sketch: matrix 0 is the single call's
     Pn, sn, inn = gl.galore_rsvd_update(Gb, r, k - r, 1, 21, 0)
     assert (inn.cpu().numpy() == 0).all() and int(iw.cpu()[0]) == 0
     assert torch.equal(Pw[0], Pn[0]) and torch.equal(sw[0], sn[0])
+    # two streams, each half a wide launch by itself but not both together
+    both = (256 + k // 8) // pairs + 1
+    assert rule("wide_pairs", k, pairs, both - both // 2, both - both // 2)
+    assert not rule("wide_pairs", k, pairs, both - both // 2, both)
+    Ga = dev_stored(G).expand(both, m, n).contiguous()
+    Pa, sa, ia = gl.galore_rsvd_update(Ga, r, k - r, 1, 21, 0, aux_stream=torch.cuda.Stream())
+    assert (ia.cpu().numpy() == 0).all()
+    assert torch.equal(Pa[:batch], Pn[:both]) and torch.equal(sa[:batch], sn[:both])
 
 
 @pytest.mark.parametrize("k", [1, 15, 17, 48, 63, 64, 65, 81, 128, 129, 145])
