@@ -200,8 +200,9 @@ GALORE_API int galore_rsvd_update_traced(const void* G, int32_t g_dtype, int64_t
  * Bytes of workspace galore_project uses for `batch` m x n matrices with rank
  * r and gradient storage g_dtype: for a bf16 gradient, the three bf16 planes
  * of P^T that feed the bf16 matrix cores and, where s is no multiple of 32 or n
- * none of 8, a copy of the gradient with both sides padded to multiples of 32;
- * 0 for an fp32 gradient (which needs none) and for invalid sizes or dtype.
+ * none of 8 and the work is worth it (s above 96, or more than 1280 tiles of 128
+ * x 128 entries of R in the batch), a copy of the gradient with both sides padded
+ * to multiples of 32; 0 for an fp32 gradient (which needs none) and for invalid sizes or dtype.
  */
 GALORE_API size_t galore_project_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch, int32_t g_dtype);
 

@@ -82,6 +82,19 @@ inline F32Tile f32_tril_tile(int M, int N, int K, int64_t batch) {
 // 264: 91 / 99).
 inline bool three_plane_half(int M, int N, int64_t batch) { return tile_count(M, N, 256, 128, batch) <= 256; }
 
+// The projection of a bf16 gradient off the 16-byte grid: planes against a padded
+// copy (three launches), or the fp32 matrix cores on the gradient as it is (one).
+// The latter is done first while the contraction is three of its 32-deep stages at
+// most and the launch has the narrow tiles to fill the chip (f32_tile: at most 1280
+// wide ones). One s x l gradient unless a batch is named, times copy / fp32 cores:
+// 24x30000, r = 4: 11 / 7 us; 8 of them, 1880 wide tiles: 25 / 35; 40x4001: 11 / 7;
+// 8 x 33x20001: 29 / 26; 8 x 64x10001, r = 64: 38 / 19; 32 of them, 2528 tiles: 92 /
+// 98; 8 x 96x10001, r = 32: 30 / 24; 8 x 80x20001, r = 8: 33 / 36; 8 x 130x10001, r =
+// 4: 28 / 31; 200x5001 r = 4: 15 / 15; 1000x4000: 33 / 40.
+inline bool padded_projection(int s, int l, int r, int64_t batch) {
+    return s > 96 || tile_count(r, l, 128, 128, batch) > 1280;
+}
+
 // The six-plane product: 128 x 128 tiles, two workgroups to a CU (rounds of 512),
 // instead of 256 x 256, one to a CU (rounds of 256). For the same work the small
 // tiles cost 1.3 times as much at K = 256 and, half round by half round, 1.4 times

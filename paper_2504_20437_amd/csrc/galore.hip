@@ -11,6 +11,7 @@
 #include "../../include/galore.h"
 
 #include "common.hpp"
+#include "dispatch.hpp"
 
 using namespace galore;
 
@@ -793,8 +794,8 @@ int galore_svd_update(const void* G, int32_t g_dtype, int64_t m, int64_t n, int6
 
 // Workspace of the projection with a bf16 gradient: the three bf16 planes of
 // P^T (r x pad8(s) each) per matrix; for a G whose rows, packed, the direct-load
-// product cannot take (copy), planes padded to 32 and the padded copy of G as
-// well. A workspace of the first size alone still serves (without the copy).
+// product cannot take, where the copy pays (copy), planes padded to 32 and the
+// padded copy of G as well. A workspace of the first size alone still serves (without the copy).
 struct ProjLayout {
     int64_t ldpl, planeStride, stridePl;
     size_t total;
@@ -809,7 +810,8 @@ ProjLayout make_proj_layout(const Shape& sh, int r, int batch) {
     pl.planeStride = pad_elems(static_cast<int64_t>(r) * pl.ldpl);
     pl.stridePl = 3 * pl.planeStride;
     pl.total = align_up(static_cast<size_t>(batch) * pl.stridePl * sizeof(uint16_t), kAlign);
-    pl.copy = sh.s % 32 != 0 || sh.n % 8 != 0;
+    pl.copy = (sh.s % 32 != 0 || sh.n % 8 != 0) &&
+              padded_projection(static_cast<int>(sh.s), static_cast<int>(sh.l), r, batch);
     pl.ldplC = pad32(sh.s);
     pl.planeStrideC = pad_elems(static_cast<int64_t>(r) * pl.ldplC);
     pl.strideGp = GradPad(sh).stride;

@@ -16,6 +16,7 @@ int narrow_sign_columns_(int rows, int r, long b) { return narrow_sign_columns(r
 int narrow_align_columns_(int r, long b) { return narrow_align_columns(r, b); }
 int f32_tile_(int M, int N, int kcontig, int adds, long b) { return f32_tile(M, N, kcontig, adds, b); }
 int f32_tril_tile_(int M, int N, int K, long b) { return f32_tril_tile(M, N, K, b); }
+int padded_projection_(int s, int l, int r, long b) { return padded_projection(s, l, r, b); }
 int three_plane_half_(int M, int N, long b) { return three_plane_half(M, N, b); }
 int six_plane_small_(int M, int N, int K, long b) { return six_plane_small(M, N, K, b); }
 int step_pairs_(int k, int block) { return step_pairs(k, block); }

@@ -1072,9 +1072,9 @@ def test_rsvd_cholesky_block_edges(gl, orc, k):
                                                 (31, 300, 301, 3, 7, 8), (257, 40, 45, 1, 33, 4), (128, 264, 272, 5, 32, 8)])
 def test_unaligned_bf16_gradient(gl, orc, m, n, ldg, off, r, bits):
     """bf16 gradients whose rows start on no 16-byte boundary, by size, by row
-    pitch or by the pointer, both orientations: the update and the projection
-    through the padded copy, which holds zeros past the matrix (the memory beside
-    G holds NaN), the projection with a workspace of the planes alone, and the
+    pitch or by the pointer, both orientations: the update through the padded
+    copy, which holds zeros past the matrix (the memory beside G holds NaN), the
+    projection with its workspace and with one of the planes alone, and the
     low-bit projection on the fp32 matrix cores."""
     import torch
     s, l = min(m, n), max(m, n)
@@ -1314,11 +1314,28 @@ def _padded_projection(gl, m, n, r, batch, ldg=None, off=0):
 def test_padded_copy_row_widths(gl, width, tall):
     """The padded copy deals a workgroup's threads out over rows by the row's
     width: every number of threads a row, rows off the workgroup's, both
-    orientations, a pitch and a pointer off the word."""
-    rows = {True: max(width + 70, 200), False: max(1, min(width // 2, 77))}[tall]
-    r = min(width, rows, 5)
-    _padded_projection(gl, rows, width, r, 2)
-    _padded_projection(gl, rows, width, r, 2, ldg=width + 3, off=1)
+    orientations, a pitch and a pointer off the word. Thin matrices take the copy
+    in batches of the size the rule names."""
+    rows = max(width + 70, 200) if tall else max(1, min(width - 31, 165))
+    s, l = min(rows, width), max(rows, width)
+    r, batch = min(s, 5), 2
+    if not rule("padded_projection", s, l, r, batch):
+        batch = 1280 // ((l + 127) // 128) + 1
+    assert rule("padded_projection", s, l, r, batch)
+    _padded_projection(gl, rows, width, r, batch)
+    _padded_projection(gl, rows, width, r, batch, ldg=width + 3, off=1)
+
+
+@pytest.mark.parametrize("m,n,r", [(97, 200, 64), (300, 101, 96), (200, 96, 7), (96, 10001, 33), (24, 40001, 8)])
+def test_ragged_projection_routes(gl, m, n, r):
+    """The ragged projection on the fp32 matrix cores and on the padded copy, at
+    and beside the rule's lines: each within the fp32 bound of fp64."""
+    s, l = min(m, n), max(m, n)
+    big = 1280 // (((l + 127) // 128) * ((r + 127) // 128)) + 1
+    assert rule("padded_projection", s, l, r, 1) == (s > 96) and rule("padded_projection", s, l, r, big)
+    assert s > 96 or not rule("padded_projection", s, l, r, big - 1)
+    for batch in (1, big - 1, big):
+        _padded_projection(gl, m, n, r, batch)
 
 
 def test_padded_copy_past_one_grid(gl):
