@@ -233,7 +233,7 @@ GALORE_API int galore_project(const float* P, int64_t ldp, int64_t stride_p, con
  * galore_project without a workspace, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving or training loops,
  * harnesses that forbid allocation): the same projection, kernels and results
- * as galore_project with a workspace of galore_project_noalloc_max_bytes()
+ * as galore_project with a workspace of galore_project_workspace_size(...)
  * bytes, with that scratch held instead in a fixed-size device array inside
  * the library (galore_project_noalloc_max_bytes() bytes, 64 MiB; one copy on
  * each device the library runs on, kept until the process ends). The caller
@@ -243,10 +243,14 @@ GALORE_API int galore_project(const float* P, int64_t ldp, int64_t stride_p, con
  * Every call on a device shares that device's array: calls that overlap on one
  * device (concurrent streams or host threads) race and must be serialised by
  * the caller. The array needs no initial contents (each call writes every byte
- * it reads).
- * Errors: as galore_project; a bf16 gradient whose planes of P^T exceed
- * galore_project_noalloc_max_bytes() -> WORKSPACE, checked before any device call; the lookup of the array failing
- * -> HIP. An fp32 gradient needs no scratch (fp32 matrix cores).
+ * it reads). Where planes and padded copies of a batch do not fit the array
+ * together, the call takes as many matrices at a time as fit, or one matrix in
+ * pieces along l, with the same results; only a gradient of which not even 32
+ * columns of A fit beside the planes of its P^T goes to the fp32 matrix cores.
+ * Errors: as galore_project; a bf16 gradient whose planes of P^T (of the whole
+ * batch) exceed galore_project_noalloc_max_bytes() -> WORKSPACE, checked before
+ * any device call; the lookup of the array failing -> HIP. An fp32 gradient needs
+ * no scratch (fp32 matrix cores).
  */
 GALORE_API size_t galore_project_noalloc_max_bytes(void);
 GALORE_API int galore_project_noalloc(const float* P, int64_t ldp, int64_t stride_p, const void* G, int32_t g_dtype,

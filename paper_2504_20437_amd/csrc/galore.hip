@@ -820,6 +820,25 @@ ProjLayout make_proj_layout(const Shape& sh, int r, int batch) {
     return pl;
 }
 
+// R = P^T A by way of the padded copy of G, with totalC bytes of the layout
+int project_padded(const float* P, int64_t ldp, int64_t stride_p, const void* G, const Shape& sh, int64_t ldg,
+                   int64_t stride_g, int r, float* R, int64_t ldr, int64_t stride_r, int batch, void* workspace,
+                   hipStream_t stream) {
+    const ProjLayout pl = make_proj_layout(sh, r, batch);
+    const GradPad gp(sh);
+    const int ks = static_cast<int>(pl.ldplC), s = static_cast<int>(sh.s), l = static_cast<int>(sh.l);
+    uint16_t* planes = static_cast<uint16_t*>(workspace);
+    uint16_t* copy = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + pl.offGp);
+    GALORE_TRY(launch_pad_bf16(G, ldg, stride_g, copy, gp.ld, gp.stride, static_cast<int>(sh.m),
+                               static_cast<int>(sh.n), static_cast<int>(gp.rows), batch, stream));
+    GALORE_TRY(launch_split3_transpose(P, ldp, stride_p, planes, pl.ldplC, pl.planeStrideC, 3 * pl.planeStrideC, s, r,
+                                       ks, batch, stream));
+    GALORE_TRY(launch_gemm_bf16x3(copy, gp.ld, gp.stride, sh.left ? 1 : 0, planes, pl.ldplC, pl.planeStrideC,
+                                  3 * pl.planeStrideC, R, ldr, stride_r, 1, l, r, ks, 1.0f, 0.0f, batch, stream,
+                                  nullptr, 0, 3, nullptr, 0, static_cast<int>(gp.ld)));
+    return GALORE_OK;
+}
+
 size_t galore_project_workspace_size(int64_t m, int64_t n, int32_t r, int32_t batch, int32_t g_dtype) {
     if (m < 1 || n < 1 || r < 1 || batch < 1 || m > INT32_MAX || n > INT32_MAX) return 0;
     if (g_dtype != GALORE_BF16) return 0;
@@ -858,21 +877,9 @@ int galore_project(const float* P, int64_t ldp, int64_t stride_p, const void* G,
                                           1.0f, 0.0f, batch, stream));
             return GALORE_OK;
         }
-        if (pl.copy && workspace_bytes >= pl.totalC) {
-            const GradPad gp(sh);
-            const int ks = static_cast<int>(pl.ldplC);
-            uint16_t* copy = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + pl.offGp);
-            GALORE_TRY(launch_pad_bf16(G, ldg, stride_g, copy, gp.ld, gp.stride, static_cast<int>(m),
-                                       static_cast<int>(n), static_cast<int>(gp.rows), batch, stream));
-            GALORE_TRY(launch_split3_transpose(P, ldp, (batch > 1) ? stride_p : sh.s * ldp, planes, pl.ldplC,
-                                               pl.planeStrideC, 3 * pl.planeStrideC, static_cast<int>(sh.s), r, ks,
-                                               batch, stream));
-            GALORE_TRY(launch_gemm_bf16x3(copy, gp.ld, gp.stride, a_mc, planes, pl.ldplC, pl.planeStrideC,
-                                          3 * pl.planeStrideC, R, ldr, stride_r, 1, static_cast<int>(sh.l), r, ks,
-                                          1.0f, 0.0f, batch, stream, nullptr, 0, 3, nullptr, 0,
-                                          static_cast<int>(gp.ld)));
-            return GALORE_OK;
-        }
+        if (pl.copy && workspace_bytes >= pl.totalC)
+            return project_padded(P, ldp, (batch > 1) ? stride_p : sh.s * ldp, G, sh, ldg, stride_g, r, R, ldr,
+                                  stride_r, batch, workspace, stream);
     }
     GemmArgs a{};
     // R (r x l) = P^T A : A-operand P^T (P[kk][i], M contiguous), B-operand A
@@ -911,9 +918,38 @@ int galore_project_noalloc(const float* P, int64_t ldp, int64_t stride_p, const 
     if (g_dtype == GALORE_F32)   // the fp32 path needs no scratch
         return galore_project(P, ldp, stride_p, G, g_dtype, m, n, ldg, stride_g, r, R, ldr, stride_r, batch, nullptr,
                               0, stream);
-    if (make_proj_layout(sh, r, batch).total > kStaticScratchBytes) return GALORE_ERR_WORKSPACE;
+    const ProjLayout pl = make_proj_layout(sh, r, batch);
+    if (pl.total > kStaticScratchBytes) return GALORE_ERR_WORKSPACE;
     void* ws = scratch_on_current_device();
     if (ws == nullptr) return GALORE_ERR_HIP;
+    if (pl.copy && pl.totalC > kStaticScratchBytes) {
+        // where planes and copy of the batch do not fit, as many matrices at a
+        // time as do, or pieces of A's l side of one: every entry of R sees the same
+        // operations, whatever piece it is in
+        const size_t room = kStaticScratchBytes - 2 * kAlign;
+        const ProjLayout one = make_proj_layout(sh, r, 1);
+        const size_t planes = 3 * one.planeStrideC * sizeof(uint16_t);
+        const size_t fit = room / (planes + one.strideGp * sizeof(uint16_t));
+        const int64_t sp = (batch > 1) ? stride_p : sh.s * ldp;
+        int64_t width = sh.l;
+        if (fit == 0) {
+            // a piece's strideGp: at most one rounding of the element count more
+            const size_t column = one.ldplC * sizeof(uint16_t);
+            width = planes + 2 * kAlign < room ? static_cast<int64_t>((room - planes - 2 * kAlign) / column) / 32 * 32 : 0;
+        }
+        const int step = static_cast<int>(std::max<size_t>(fit, 1));
+        for (int b = 0; width > 0 && b < batch; b += step)
+            for (int64_t c = 0; c < sh.l; c += width) {
+                Shape piece = sh;
+                piece.l = std::min(width, sh.l - c);
+                (sh.left ? piece.n : piece.m) = piece.l;
+                const uint16_t* g = static_cast<const uint16_t*>(G) + b * stride_g + c * (sh.left ? 1 : ldg);
+                GALORE_CHECK(project_padded(P + b * sp, ldp, sp, g, piece, ldg, stride_g, r, R + b * stride_r + c, ldr,
+                                            stride_r, std::min(step, batch - b), ws, stream));
+            }
+        if (width > 0) return GALORE_OK;
+        // not even 32 columns of one matrix fit beside its planes: the fp32 cores
+    }
     return galore_project(P, ldp, stride_p, G, g_dtype, m, n, ldg, stride_g, r, R, ldr, stride_r, batch, ws,
                           kStaticScratchBytes, stream);
 }
