@@ -5,7 +5,7 @@
 //    v_mfma_f32_32x32x2_f32. gfx950 has no TF32 matrix path, so fp32 MFMA is
 //    the precision the method is computed in. bf16-stored gradients are
 //    widened exactly to fp32 while staging into LDS.
-//    Workgroup tile 128 x 128 x 32 (or 64 x 64 x 64 for launches of few tiles),
+//    Workgroup tile 128 x 128 x 32 (or a 64 x 64 one, by the sizes of a launch),
 //    four wave64s in a 2 x 2 arrangement, each wave owning a 64 x 64 (32 x 32)
 //    sub-tile (2 x 2 MFMA 32x32 blocks, or one). LDS holds A^T
 //    and B tiles in M-/N-contiguous order so that the per-lane MFMA operand

@@ -220,20 +220,23 @@ __device__ __forceinline__ bf16x8 apply_frag(const unsigned char* lds, int s, in
     return __builtin_shufflevector(q[0], q[1], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Element type of the inner sweep's Gram and accumulated rotation. fp32: the
-// rotation is applied to fp32 columns on the fp32 matrix cores anyway, the
-// sweep only has to produce an orthogonal Theta that reduces the pair's
-// off-diagonal; the pair Gram, the convergence test, the diagonal the sweep
-// carries and the rotation angles stay fp64, so pairs are judged converged
-// (and the last sweeps are steered) at fp64 accuracy.
-typedef float jreal;
+// The inner sweep's Gram and accumulated rotation are fp32: the rotation is
+// applied to fp32 columns (split exactly into planes), and the sweep only has to
+// produce an orthogonal Theta that reduces the pair's off-diagonal. The pair
+// Gram, the convergence test, the diagonal the sweep carries and the rotation
+// angles' differences stay fp64, so pairs are judged converged (and the last
+// sweeps are steered) at fp64 accuracy.
 
 // Angles at and below which a pair's rotations are taken all at once: every
-// |E_ij| <= kSmallAngle and the sum of E_ij^2 over i < j <= kSmallSum, i.e.
-// |E|_2 <= 0.15 (an antisymmetric matrix's singular values come in pairs).
+// |E_ij| <= kSmallAngle and the sum of E_ij^2 over i < j <= kSmallSum. The terms
+// are cut off to units of 2^-24, so the true sum may be 2016 units, 1.2e-4, larger:
+// |E|_2^2 <= 0.02262, |E|_2 <= 0.1504 (an antisymmetric matrix's singular values
+// come in pairs).
 constexpr float kSmallAngle = 0.1f;
 constexpr float kSmallSum = 0.0225f;
-constexpr float kTinySum = 1.0f / 8192.0f;   // below: two products give Theta to fp32 rounding
+// below (|P|_2 <= 2.43e-4 with the cut-off): two products give Theta to fp32
+// rounding, off an orthogonal matrix by 3/8 |P|^2 < 2.3e-8
+constexpr float kTinySum = 1.0f / 8192.0f;
 constexpr int SP = JW + 4;                   // row pitch of E and S (fp32): 16-byte rows, fragment reads on distinct banks
 
 // LDS of one group of four waves, reused phase by phase: two plane chunks, the
@@ -252,7 +255,7 @@ __device__ __forceinline__ int seg_begin(int nchunk, int g) { return (g * nchunk
 // polar factor of I + E (E antisymmetric),
 //   Theta = (I + E)(I - E^2)^(-1/2) = (I + E)(I + S),
 //   S = P/2 + 3/8 P^2 + 5/16 P^3 + ...,  P = E^2,
-// off an orthogonal matrix by 35/128 |P|^4 < 7e-8. Second-order terms are left
+// off an orthogonal matrix by 35/128 |P|^4 < 7.2e-8. Second-order terms are left
 // for the next sweep, as a sweep of single rotations leaves them: in a CPU
 // model of these sweeps (six spectra, k = 136 .. 528, the exact SVD among
 // them) the number of sweeps is unchanged and the number of pair rotations

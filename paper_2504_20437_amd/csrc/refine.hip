@@ -392,9 +392,9 @@ __global__ __launch_bounds__(256) void refine_update_kernel(const double* Mb, in
 }
 
 // Order the refined vectors by lambda (descending, ties by index; a NaN last):
-// permb[b][j] = index of the j-th, sigma_j = sqrt(lambda). One thread per
-// vector, its rank the number of vectors ahead of it; grid (ceil(k / 32),
-// batch), each workgroup with the matrix's lambdas in LDS (dynamic: k doubles).
+// permb[b][j] = index of the j-th, sigma_j = sqrt(lambda). The rank of a vector is
+// the number of vectors ahead of it, counted by eight threads; grid (ceil(k /
+// 32), batch), each workgroup with the matrix's lambdas in LDS (dynamic: k doubles).
 __global__ __launch_bounds__(256) void refine_rank_kernel(const double* lamb, int k, int r, int* permb, float* sigma,
                                                           int64_t stride_sigma, const int* flags) {
     const int b = blockIdx.y;
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256) void refine_rank_kernel(const double* lamb, in
         lam[i] = (v == v) ? v : -DBL_MAX;
     }
     __syncthreads();
-    // eight threads a column, as the column order of the sweeps
+    // eight threads a vector, as in the column order of the sweeps
     const int c = 32 * blockIdx.x + (threadIdx.x >> 3);
     const double vc = lam[min(c, k - 1)];
     int rank = 0;

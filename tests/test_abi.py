@@ -52,7 +52,7 @@ def test_workspace_size():
     assert gl.galore_rsvd_workspace_size(1056, 600000, 1024, 32, 1) > 0
     assert gl.galore_rsvd_workspace_size(1056, 700000, 1024, 32, 1) == 0
     assert gl.galore_rsvd_workspace_size(300000, 4096, 4000, 96, 1) == 0
-    # a bf16 gradient also keeps room for its transposed copy and the split sketch operand
+    # a bf16 gradient also keeps room for its padded copy and the split sketch operand
     import torch
     bf = gl.galore_rsvd_workspace_size(4096, 11008, 1024, 32, 1, torch.bfloat16)
     assert bf >= one + 2 * 4096 * 11008 + 3 * 2 * 1056 * 11008
