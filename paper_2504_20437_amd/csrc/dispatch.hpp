@@ -120,7 +120,8 @@ inline bool six_plane_small(int M, int N, int K, int64_t batch) {
 // the chunk loops are (k = 1056, 272: 21.6, 25.6 ms; 352: 24.9, 26.6; 384: 24.9,
 // 25.9; 448: 29.2, 27.9; 512: 31.1, 28.1; k = 528, 320: 8.5, 8.7; 384: 9.5, 8.9; k
 // = 136, 260: 2.7, 2.8; 300: 1.71, 1.64; k = 40, 300: 0.48, 0.43; k = 2048, 480:
-// 84.0, 88.4; 512: 94.5, 88.7).
+// 84.0, 88.4; 512: 94.5, 88.7; whole update, k = 2560, 480: 193, 219; k = 4096, 512:
+// 508, 616).
 // (pairs of a step of k columns in blocks: an odd number of blocks, at least three,
 // has a padding block, whose pair is not launched)
 inline int step_pairs(int k, int block) {
@@ -128,7 +129,7 @@ inline int step_pairs(int k, int block) {
     return real % 2 != 0 && real >= 3 ? real / 2 : (real + 1) / 2;
 }
 inline bool wide_pairs(int k, int pairs, int64_t batch, int64_t in_flight) {
-    return pairs * batch <= 256 && pairs * in_flight <= 256 + (k < 1792 ? k : 1792) / 8;
+    return pairs * batch <= 256 && pairs * in_flight < 256 + k / 8;
 }
 
 }  // namespace galore

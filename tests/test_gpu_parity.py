@@ -1034,7 +1034,7 @@ def test_rsvd_pair_launch_forms_agree(gl, orc, k):
     assert (inn.cpu().numpy() == 0).all() and int(iw.cpu()[0]) == 0
     assert torch.equal(Pw[0], Pn[0]) and torch.equal(sw[0], sn[0])
     # two streams, each half a wide launch by itself but not both together
-    both = (256 + k // 8) // pairs + 1
+    both = -(-(256 + k // 8) // pairs)
     assert rule("wide_pairs", k, pairs, both - both // 2, both - both // 2)
     assert not rule("wide_pairs", k, pairs, both - both // 2, both)
     Ga = dev_stored(G).expand(both, m, n).contiguous()
