@@ -16,13 +16,17 @@ inline int64_t tile_count(int M, int N, int tile_m, int tile_n, int64_t batch) {
 // columns and 512 threads instead of 64 columns and 256, while the latter would
 // leave CUs idle. A 16-column workgroup reads 64-byte pieces of rows and moves
 // half the bytes per second once the chip is full.
-//   sign (whole stage): 4096x1024 projectors, 1: 100 -> 45 us; 8 (128 workgroups of
-//   64 columns): 160 -> 117; 10: 171 against 180 narrow; 25: 313 against 417; 64:
-//   663 against 988. 2048x256: 40: 87 -> 82, 64: 114 against 147. Below 1024 rows
-//   combining 128 row groups costs more than the scan saves (512x128, 1: 27.5
-//   against 29.4, 64: 29.9 against 38.4).
-inline bool narrow_sign_columns(int rows, int r, int64_t batch) {
-    return rows >= 1024 && static_cast<int64_t>((r + 63) / 64) * batch < 144;
+//   sign (whole stage, n = workgroups of 64 columns; wide / narrow us): combining the
+//   128 row groups costs more than the scan of few rows saves. Rows on 16 bytes:
+//   512x128, n = 2: 27 / 29; 640x200, 4: 31 / 30, 32: 32 / 32, 64: 33 / 36; 768x200,
+//   32: 35 / 34, 64: 36 / 38; 1000x200, 64: 46 / 43, 128: 53 / 54; 2048x256, 128: 86 /
+//   72, 160: 87 / 82, 256: 114 / 147; 4096x1024, 16: 100 / 45, 128: 160 / 117, 160: 171
+//   / 180, 1024: 663 / 988. Others (single loads): 128x65, 2: 26 / 28; 256x65, 32: 34 /
+//   31, 128: 36 / 37; 512x127, 128: 59 / 53, 200: 63 / 71; 1000x201, 200: 106 / 96, 256:
+//   110 / 113; 4096x1023, 160: 359 / 311, 256: 398 / 477.
+inline bool narrow_sign_columns(int rows, int r, bool vec, int64_t batch) {
+    const int64_t blocks = static_cast<int64_t>((r + 63) / 64) * batch;
+    return vec ? blocks < (rows < 1088 ? (rows - 512) / 4 : 144) : blocks < (rows < 528 ? (rows - 160) / 2 : 184);
 }
 //   switch: 4096x1024, 1: 39 -> 19 us; 6 (96 workgroups): 66 -> 65; 7: 66 against 69
 //   narrow, 8: 67 against 80, 64: 364 against 682; 1024x256, 32: 18 against 22.
@@ -61,15 +65,18 @@ inline F32Tile f32_tile(int M, int N, bool a_kcontig, bool adds, int64_t batch) 
     return kTile64x4;
 }
 // The triangular product Y R^-1 (fp32 output): the wide tile's 4 x 1 waves or the
-// deep narrow tile. The launch ends with the longest column tile, K deep, and the
-// narrow tiles' extra rounds fill its time the better the larger K is: k = 72, t =
-// 512: 48 narrow, 65 wide, t = 1024: 82, 69; k = 136, t = 576: 62, 71, t = 624: 80,
-// 71; k = 272, t = 960: 125, 133, t = 1040: 144, 136, t = 1680: 199, 148; k = 528,
-// t = 1728: 274, 279, t = 2016: 334, 295; k = 1056, t = 1596: 448, 474.
+// deep narrow tile, which wins its first round of 512 at every k. Past it the
+// launch waits for its longest column tile, K deep, and further narrow rounds fit
+// into that time the better the larger K is (k: t: narrow / wide us): 24: 512: 20 /
+// 20, 576: 27 / 21; 72: 512: 25 / 33, 640: 33 / 33, 800: 37 / 34; 112: 704: 40 / 46,
+// 800: 45 / 46; 136: 576: 32 / 37, 624: 41 / 37; 200: 768: 49 / 56, 896: 59 / 57; 272:
+// 960: 125 / 133, 1040: 144 / 136, 1680: 199 / 148; 368: 1536: 98 / 120, 1728: 119 /
+// 119; 528: 1728: 274 / 279, 2016: 334 / 295; 640: 1920: 150 / 172; 1056: 1596: 448 /
+// 474.
 inline F32Tile f32_tril_tile(int M, int N, int K, int64_t batch) {
     const int64_t wide = tile_count(M, N, 128, 128, batch), narrow = tile_count(M, N, 64, 64, batch);
-    const int64_t deep = static_cast<int64_t>(K) * 18 / 5;   // 3.6 K
-    return wide <= 512 && narrow <= (deep > 608 ? deep : 608) ? kTile64 : kTile128;
+    const int64_t most = K <= 40 ? 512 : (K > 96 && K <= 128) ? 800 : K < 176 ? 608 : static_cast<int64_t>(K) * 21 / 5;
+    return wide <= 512 && narrow <= most ? kTile64 : kTile128;
 }
 
 // The products of one or three bf16 planes (bf16x3.hip), two workgroups to a CU:
@@ -97,16 +104,16 @@ inline bool padded_projection(int s, int l, int r, int64_t batch) {
 
 // The six-plane product: 128 x 128 tiles, two workgroups to a CU (rounds of 512),
 // instead of 256 x 256, one to a CU (rounds of 256). For the same work the small
-// tiles cost 1.3 times as much at K = 256 and, half round by half round, 1.4 times
-// at larger K; they win where the wide ones leave their last round nearly empty
+// tiles cost 1.3 times as much up to K = 320 and, half round by half round, 1.4
+// times beyond; they win where the wide ones leave their last round nearly empty
 // (back-projection, small / wide tiles, us; T wide ones): K = 1024, T = 64: 80 /
 // 145, 128: 137 / 154, 152: 178 / 154, 260: 303 / 333, 320: 339 / 352, 352: 386 /
 // 357, 384: 409 / 367, 520: 572 / 559; K = 512, 320: 179 / 191, 352: 206 / 194; K =
-// 256, 320: 103 / 118, 352: 113 / 117, 420: 129 / 121, 688: 229 / 208; K = 64, 384:
+// 256, 320: 103 / 118, 352: 113 / 117, 420: 129 / 121, 688: 229 / 208; K = 288, 375: 2% less; K = 64, 384:
 // 59 / 63, 508: 75 / 73).
 inline bool six_plane_small(int M, int N, int K, int64_t batch) {
     const int64_t wide = tile_count(M, N, 256, 256, batch), small = tile_count(M, N, 128, 128, batch);
-    const int64_t cost = K <= 256 ? 13 * ((small + 511) / 512) : 7 * ((small + 255) / 256);
+    const int64_t cost = K < 320 ? 13 * ((small + 511) / 512) : 7 * ((small + 255) / 256);
     return cost < 20 * ((wide + 255) / 256);
 }
 

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const float* src, int64_
 hipError_t launch_sign_fix(float* P, int rows, int r, int64_t ldp, int64_t strideP, int batch,
                            hipStream_t stream) {
     const int vec = (ldp % 4 == 0) && (batch == 1 || strideP % 4 == 0) && (reinterpret_cast<uintptr_t>(P) % 16 == 0);
-    if (narrow_sign_columns(rows, r, batch))
+    if (narrow_sign_columns(rows, r, vec != 0, batch))
         hipLaunchKernelGGL((sign_fix_kernel<16, 32>), dim3((r + 15) / 16, batch), dim3(512), 0, stream, P, rows, r, ldp,
                            strideP, vec);
     else

@@ -12,7 +12,7 @@ SHIM = """
 #include "dispatch.hpp"
 using namespace galore;
 extern "C" {
-int narrow_sign_columns_(int rows, int r, long b) { return narrow_sign_columns(rows, r, b); }
+int narrow_sign_columns_(int rows, int r, int vec, long b) { return narrow_sign_columns(rows, r, vec, b); }
 int narrow_align_columns_(int r, long b) { return narrow_align_columns(r, b); }
 int f32_tile_(int M, int N, int kcontig, int adds, long b) { return f32_tile(M, N, kcontig, adds, b); }
 int f32_tril_tile_(int M, int N, int K, long b) { return f32_tril_tile(M, N, K, b); }
